@@ -81,6 +81,34 @@ def test_prefill_matches_oracle(name):
     say(f"[gpu] prefill {name}: worst output rel err {worst:.2e}")
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("Hq,Hkv", [(8, 2), (6, 3)])      # Hq % 8 == 0: head order by XCD
+@pytest.mark.parametrize("T,lens", [(1, [1, 1]), (32, [32, 31]), (33, [33, 1]), (64, [64, 63]),
+                                    (97, [96, 97]), (128, [128, 65]), (300, [33, 300])])
+def test_prefill_unit_edges(d, Hq, Hkv, T, lens):
+    """Lengths around the 32-key units, 64-key blocks and 128-row workgroups, the
+    unit before the first (no weights) and sequences that end inside a wavefront."""
+    q, k, v, tau = _inputs(2, Hq, Hkv, T, d, seed=31 * T + d + Hq)
+    dev = torch.device("cuda")
+    sl = torch.tensor(lens, dtype=torch.int32, device=dev)
+    for add in (False, True):
+        out, R, L = eta.gated_prefill(q.to(dev), k.to(dev), v.to(dev), tau.to(dev), sl, beta=4.0,
+                                      additive=add, C=2.0)
+        torch.cuda.synchronize()
+        r = oracle.prefill(as_numpy(q), as_numpy(k), as_numpy(v), tau.numpy().astype(np.float64),
+                           lens, beta=4.0, additive=add, C=2.0)
+        o, Rg, Lg = out.float().cpu().numpy(), R.cpu().numpy(), L.cpu().numpy()
+        for b in range(2):
+            n = lens[b]
+            assert np.all(o[b, :, n:] == 0) and np.all(Rg[b, :, n:] == 0)
+            assert np.all(np.isneginf(Lg[b, :, n:]))
+            for h in range(Hq):
+                ref = r.o[b, h, :n]
+                assert np.max(np.abs(o[b, h, :n] - ref)) <= 2e-2 * np.max(np.abs(ref)), (add, b, h)
+            np.testing.assert_allclose(Rg[b, :, :n], r.r[b, :, :n], rtol=1e-4, atol=1e-5)
+            np.testing.assert_allclose(Lg[b, :, :n], r.lse[b, :, :n], rtol=0, atol=1e-4)
+
+
 def _check_rows(o, R, L, r, rows, lens):
     worst = 0.0
     for n, (b, h, i) in enumerate(rows):
