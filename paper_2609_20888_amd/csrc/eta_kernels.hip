@@ -1862,21 +1862,32 @@ __global__ __launch_bounds__(64 * kSplitWaves) void split_kernel(SplitArgs a) {
 
 // ---------------------------------------------------------------- calibration
 //
-// Offline density-matched calibration.  calib_kernel: one workgroup per
-// (query head, sequence); wavefront w takes the 16-query groups w, w + 4, ...
-// and, for each, the 16-key blocks 0 .. group (the causal triangle).  Scores
-// come from v_mfma_f32_16x16x32_bf16 in the standard layout: A = 16 query rows
-// x 32 dims, B = 32 dims x 16 keys, so lane l gets the scores of queries
-// 4 (l >> 4) + i of the group and key l & 15 of the block.  Each causal score
-// adds its step's weight round(2^40 / (t + 1)) to an LDS histogram with a
-// 64-bit integer atomic; the lane's gate sum sigmoid(beta (S - tau_t)) / (t + 1)
-// accumulates in fp64 in a fixed order and is added once, rounded to the same
-// fixed point.  Integer sums make the result independent of the adds' order.
-// calib_solve_kernel: one workgroup per head, fp64 bisection of the
-// histogram's density function with fixed-order block reductions.
+// Offline density-matched calibration.  calib_kernel: the queries of a (query
+// head, sequence) are cut into blocks of 64; a wavefront takes a block and walks
+// the causal keys 16 at a time, so a tile of keys, loaded once (the next tile
+// while this one is used), serves four 16-query groups.  Scores come from
+// v_mfma_f32_16x16x32_bf16 in the standard layout: A = 16 query rows x 32 dims,
+// B = 32 dims x 16 keys, so lane l gets the scores of queries 4 (l >> 4) + i of a
+// group and key l & 15 of the tile.  Each causal score adds its step's weight
+// round(2^40 / (t + 1)) to the workgroup's LDS histogram with a 64-bit integer
+// atomic; the lane's gate sum sigmoid(beta (S - tau_t)) / (t + 1) accumulates in
+// fp64 in a fixed order and is added once, rounded to the same fixed point.
+// Integer sums make the result independent of the adds' order; the blocks are
+// dealt by the number of steps alone, so calls over parts of the sequences add
+// up to the same integers.  Only a group's diagonal tile is masked; rows past the
+// last step carry zero weight.  The workgroup's four blocks are neighbours (equal
+// causal ranges), the longest first.
+// Bound by the vector unit (17 instructions, 19 issue slots per score) and, behind it,
+// the LDS atomics (60% busy): eight sequences of 2048 steps, 32/8 heads, d = 128
+// (537 M causal pairs): 2.11 -> 0.37 ms against one workgroup per (head, sequence) that
+// loaded each tile of keys for one 16-query group and masked every tile.
+// calib_solve_kernel: one workgroup per head, safeguarded Newton iteration in
+// fp64 on the histogram's density function with fixed-order block reductions.
 
+#if ETA_PART == 0
 constexpr int kCalibMaxBins = 4096;
 constexpr double kCalibUnit = 1099511627776.0;   // 2^40
+constexpr int kCalibQ = 64;                      // queries per block
 
 struct CalibArgs {
   const uint16_t* q;
@@ -1889,11 +1900,12 @@ struct CalibArgs {
 };
 
 template <int D>
-__global__ __launch_bounds__(256) void calib_kernel(CalibArgs a) {
+__global__ __launch_bounds__(256, 2) void calib_kernel(CalibArgs a) {
   constexpr int KC = D / 32;                      // 32-dim chunks
+  constexpr int NG = kCalibQ / 16;                // 16-query groups of a block
   __shared__ unsigned long long hist_s[kCalibMaxBins];
   const int h = blockIdx.x, x = blockIdx.y, tid = threadIdx.x;
-  const int lane = tid & 63, w = tid >> 6;
+  const int lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int G = a.Hq / a.Hkv;
   for (int b = tid; b < a.nb; b += 256) hist_s[b] = 0ull;
   __syncthreads();
@@ -1901,49 +1913,87 @@ __global__ __launch_bounds__(256) void calib_kernel(CalibArgs a) {
   const uint16_t* kh = a.k + (((int64_t)x * a.Hkv + h / G) * a.T) * D;
   const float* tauh = a.tau + ((int64_t)x * a.Hq + h) * a.T;
   const float scale = 1.0f / sqrtf((float)D);
-  const int ngroups = (a.T + 15) / 16;
+  const float nbl2 = -a.beta * 1.4426950408889634f;
+  const float top = (float)a.nb - 0.5f;           // truncates to the last bin
+  const int nq = (a.T + kCalibQ - 1) / kCalibQ;
   const int r16 = lane & 15, g4 = lane >> 4;
+  const int qb = nq - 1 - (4 * (int)blockIdx.z + w);
   double dens = 0.0;
-  for (int qg = w; qg < ngroups; qg += 4) {
-    // A: query row 16 qg + r16, dims 32 kc + 8 g4 .. + 7 (rows past T read row T - 1)
-    const int qr = min(16 * qg + r16, a.T - 1);
-    bf16x8 qa[KC];
+  if (qb >= 0) {
+    // A: query rows 64 qb + 16 g + r16, dims 32 kc + 8 g4 .. + 7 (rows past T read row
+    // T - 1); this lane's output rows are steps t = 64 qb + 16 g + 4 g4 + i
+    bf16x8 qa[NG][KC];
+    float tau_i[NG][4], invt_i[NG][4];
+    unsigned long long wt_i[NG][4];
 #pragma unroll
-    for (int kc = 0; kc < KC; ++kc)
-      qa[kc] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(qh + (int64_t)qr * D + 32 * kc + 8 * g4));
-    // this lane's output rows: steps t_i = 16 qg + 4 g4 + i
-    int t_i[4];
-    float tau_i[4], invt_i[4];
-    unsigned long long wt_i[4];
+    for (int g = 0; g < NG; ++g) {
+      const int qr = min(kCalibQ * qb + 16 * g + r16, a.T - 1);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      t_i[i] = 16 * qg + 4 * g4 + i;
-      const int tc = min(t_i[i], a.T - 1);
-      tau_i[i] = tauh[tc];
-      invt_i[i] = 1.0f / (float)(t_i[i] + 1);
-      wt_i[i] = (unsigned long long)llrint(kCalibUnit / (double)(t_i[i] + 1));
+      for (int kc = 0; kc < KC; ++kc)
+        qa[g][kc] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(qh + (int64_t)qr * D + 32 * kc + 8 * g4));
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int t = kCalibQ * qb + 16 * g + 4 * g4 + i;
+        const bool ok = t < a.T;
+        tau_i[g][i] = tauh[ok ? t : a.T - 1];
+        invt_i[g][i] = ok ? 1.0f / (float)(t + 1) : 0.f;
+        wt_i[g][i] = ok ? (unsigned long long)llrint(kCalibUnit / (double)(t + 1)) : 0ull;
+      }
     }
-    for (int kb = 0; kb <= qg; ++kb) {
-      const int kr = min(16 * kb + r16, a.T - 1);
-      bf16x8 kk[KC];
+    auto load = [&](int kt, bf16x8 (&kk)[KC]) {
+      const int kr = min(16 * kt + r16, a.T - 1);
 #pragma unroll
       for (int kc = 0; kc < KC; ++kc)
         kk[kc] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(kh + (int64_t)kr * D + 32 * kc + 8 * g4));
-      f32x4 c = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int kc = 0; kc < KC; ++kc) c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qa[kc], kk[kc], c, 0, 0, 0);
-      const int s_idx = 16 * kb + r16;
+    };
+    // one 16 x 16 tile of group g: the histogram and gate sums of its pairs
+    auto tile = [&](int g, const f32x4& c, int kt, auto diag_tag) {
+      constexpr bool DIAG = decltype(diag_tag)::value;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        if (s_idx <= t_i[i] && t_i[i] < a.T) {
-          const float S = c[i] * scale;
-          float f = floorf((S - a.lo) * a.inv_w);
-          f = f >= 0.f ? f : 0.f;        // also NaN
-          const int bin = f < (float)a.nb ? (int)f : a.nb - 1;
-          atomicAdd(&hist_s[bin], wt_i[i]);
-          const float gate = 1.0f / (1.0f + __expf(-a.beta * (S - tau_i[i])));
-          dens += (double)(gate * invt_i[i]);
-        }
+        const bool on = !DIAG || r16 <= 4 * g4 + i;
+        const float S = c[i] * scale;
+        // bin clamped to [0, nb): the clamped value truncates to floor; NaN gives 0
+        const int bin = (int)__builtin_amdgcn_fmed3f((S - a.lo) * a.inv_w, 0.f, top);
+        atomicAdd(&hist_s[bin], on ? wt_i[g][i] : 0ull);
+        // gate 1 / (1 + e), reciprocal and one Newton step; e = inf gives 0 (the clamp
+        // takes the step's inf * 0)
+        const float den = 1.0f + __builtin_amdgcn_exp2f((S - tau_i[g][i]) * nbl2);
+        const float y = __builtin_amdgcn_rcpf(den);
+        const float gate = __builtin_amdgcn_fmed3f(fmaf(fmaf(-den, y, 1.0f), y, y), 0.f, 1.f);
+        dens += (double)(on ? gate * invt_i[g][i] : 0.f);
+      }
+    };
+    auto mma = [&](int g, const bf16x8 (&kk)[KC]) {
+      f32x4 c = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int kc = 0; kc < KC; ++kc) c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qa[g][kc], kk[kc], c, 0, 0, 0);
+      return c;
+    };
+    constexpr std::integral_constant<bool, false> full{};
+    constexpr std::integral_constant<bool, true> diag{};
+    const int kt0 = NG * qb;                      // first of the block's diagonal tiles
+    bf16x8 kk[KC], kn[KC];
+    load(0, kk);
+    for (int kt = 0; kt < kt0; ++kt) {
+      load(kt + 1, kn);
+      f32x4 c[NG];
+#pragma unroll
+      for (int g = 0; g < NG; ++g) c[g] = mma(g, kk);
+#pragma unroll
+      for (int g = 0; g < NG; ++g) tile(g, c[g], kt, full);
+#pragma unroll
+      for (int kc = 0; kc < KC; ++kc) kk[kc] = kn[kc];
+    }
+#pragma unroll
+    for (int j = 0; j < NG; ++j) {                // tile kt0 + j: group j's diagonal
+      if (j + 1 < NG) load(kt0 + j + 1, kn);
+      tile(j, mma(j, kk), kt0 + j, diag);
+#pragma unroll
+      for (int g = j + 1; g < NG; ++g) tile(g, mma(g, kk), kt0 + j, full);
+      if (j + 1 < NG) {
+#pragma unroll
+        for (int kc = 0; kc < KC; ++kc) kk[kc] = kn[kc];
       }
     }
   }
@@ -1958,23 +2008,30 @@ __global__ __launch_bounds__(256) void calib_kernel(CalibArgs a) {
     if (v != 0ull) atomicAdd(&a.hist[(int64_t)h * a.nb + b], v);
   }
 }
-
-__device__ __forceinline__ double sigmoid_f64(double x) {
-  if (x >= 0.0) return 1.0 / (1.0 + exp(-x));
-  const double e = exp(x);
-  return e / (1.0 + e);
+// Sum over the wavefront in every lane, in a fixed order (the steps of wave_reduce
+// on both halves of the doubles).
+__device__ __forceinline__ double wave_sum_f64(double x) {
+  auto dpp = [](double v, auto ctrl) {
+    const uint2 u = __builtin_bit_cast(uint2, v);
+    constexpr int C = decltype(ctrl)::value;
+    return __builtin_bit_cast(double, make_uint2((uint32_t)__builtin_amdgcn_update_dpp(0, (int)u.x, C, 0xf, 0xf, false),
+                                                 (uint32_t)__builtin_amdgcn_update_dpp(0, (int)u.y, C, 0xf, 0xf, false)));
+  };
+  x += dpp(x, std::integral_constant<int, 0xB1>{});
+  x += dpp(x, std::integral_constant<int, 0x4E>{});
+  x += dpp(x, std::integral_constant<int, 0x141>{});
+  x += dpp(x, std::integral_constant<int, 0x140>{});
+  uint2 u = __builtin_bit_cast(uint2, x);
+  auto lo = __builtin_amdgcn_permlane16_swap(u.x, u.x, false, false);
+  auto hi = __builtin_amdgcn_permlane16_swap(u.y, u.y, false, false);
+  x = __builtin_bit_cast(double, make_uint2(lo[0], hi[0])) + __builtin_bit_cast(double, make_uint2(lo[1], hi[1]));
+  u = __builtin_bit_cast(uint2, x);
+  lo = __builtin_amdgcn_permlane32_swap(u.x, u.x, false, false);
+  hi = __builtin_amdgcn_permlane32_swap(u.y, u.y, false, false);
+  return __builtin_bit_cast(double, make_uint2(lo[0], hi[0])) + __builtin_bit_cast(double, make_uint2(lo[1], hi[1]));
 }
 
-__device__ __forceinline__ double block_sum_f64(double x, double* red) {
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
-  if (lane == 0) red[w] = x;
-  __syncthreads();
-  const double r = ((red[0] + red[1]) + red[2]) + red[3];
-  __syncthreads();
-  return r;
-}
+constexpr int kSolveWaves = 16, kSolveThreads = 64 * kSolveWaves;
 
 struct CalibSolveArgs {
   const unsigned long long* hist;
@@ -1985,35 +2042,97 @@ struct CalibSolveArgs {
   double beta, lo, hi;
 };
 
-#if ETA_PART == 0
-__global__ __launch_bounds__(256) void calib_solve_kernel(CalibSolveArgs a) {
-  constexpr int PER = kCalibMaxBins / 256;
-  __shared__ double red[4];
-  const int h = blockIdx.x, tid = threadIdx.x;
+// g(c) = sum_b H_b sigmoid(beta (s_b - c)) falls monotonically from 1 to 0; the
+// root of g(c) = target.  A first guess comes from three rounds in fp32 in which
+// every wavefront evaluates g at one of 16 points dividing the current interval;
+// then safeguarded Newton in fp64: a bracket [lo, hi] is kept as in bisection, the
+// next point is the Newton step where it lies inside the bracket, else the
+// midpoint.  Newton converges quadratically: after a step below 1e-9 / beta the
+// remaining error is below 1e-17 / beta.  One workgroup per head, sums in a fixed
+// order, all latency: bisection to adjacent fp64 values took 60 evaluations of
+// sixteen bins a thread, 142 us for 1024 bins; this takes 16 us.
+__global__ __launch_bounds__(kSolveThreads) void calib_solve_kernel(CalibSolveArgs a) {
+  constexpr int PER = kCalibMaxBins / kSolveThreads;
+  __shared__ double red[2][kSolveWaves][2];
+  __shared__ float h_s[kCalibMaxBins];
+  __shared__ float g_s[2][kSolveWaves];
+  const int h = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const double w = (a.hi - a.lo) / (double)a.nb;
-  double hb[PER], sb[PER];
+  double hb[PER];
   double tot = 0.0;
 #pragma unroll
   for (int r = 0; r < PER; ++r) {
-    const int b = tid + 256 * r;
+    const int b = tid + kSolveThreads * r;
     hb[r] = b < a.nb ? (double)a.hist[(int64_t)h * a.nb + b] : 0.0;
-    sb[r] = a.lo + ((double)b + 0.5) * w;
+    h_s[b] = (float)hb[r];
     tot += hb[r];
   }
-  tot = block_sum_f64(tot, red);
+  // workgroup sums of two values (the buffers alternate: one barrier each)
+  auto sum2 = [&](int par, double& x, double& y) {
+    x = wave_sum_f64(x);
+    y = wave_sum_f64(y);
+    if (lane == 0) {
+      red[par][wv][0] = x;
+      red[par][wv][1] = y;
+    }
+    __syncthreads();
+    x = y = 0.0;
+#pragma unroll
+    for (int k = 0; k < kSolveWaves; ++k) {
+      x += red[par][k][0];
+      y += red[par][k][1];
+    }
+  };
+  double unused = 0.0;
+  sum2(1, tot, unused);
   const double target = (double)a.dens[h] / tot;
   double lo = a.lo - 60.0 / a.beta, hi = a.hi + 60.0 / a.beta;
-  for (int it = 0; it < 2048; ++it) {
-    const double m = 0.5 * (lo + hi);
-    if (m <= lo || m >= hi) break;
-    double g = 0.0;
+  double m = 0.5 * (lo + hi);
+  if (tot > 0.0) {
+    const float want = (float)((double)a.dens[h]), nbl2 = (float)(-a.beta * 1.4426950408889634);
+    double x0 = lo, x1 = hi;
+    for (int it = 0; it < 3; ++it) {
+      const double dx = (x1 - x0) / (kSolveWaves + 1);
+      const float c = (float)(x0 + dx * (wv + 1));
+      float g = 0.f;
+#pragma unroll 8
+      for (int b = lane; b < a.nb; b += 64)
+        g = fmaf(h_s[b], __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(
+                             nbl2 * ((float)(a.lo + ((double)b + 0.5) * w) - c))), g);
+      g = wave_sum(g);
+      if (lane == 0) g_s[it & 1][wv] = g;
+      __syncthreads();
+      int above = 0;                              // points where g still exceeds the target
 #pragma unroll
-    for (int r = 0; r < PER; ++r) g += hb[r] * sigmoid_f64(a.beta * (sb[r] - m));
-    g = block_sum_f64(g, red) / tot;
-    if (g > target) lo = m; else hi = m;
+      for (int k = 0; k < kSolveWaves; ++k) above += g_s[it & 1][k] > want ? 1 : 0;
+      x1 = x0 + dx * (above + 1);
+      x0 += dx * above;
+    }
+    m = 0.5 * (x0 + x1);
+    for (int it = 0; it < 2048; ++it) {
+      double g = 0.0, dg = 0.0;
+#pragma unroll
+      for (int r = 0; r < PER; ++r) {
+        if (kSolveThreads * r < a.nb) {
+          const double x = a.beta * (a.lo + ((double)(tid + kSolveThreads * r) + 0.5) * w - m);
+          const double e = exp(-fabs(x)), s = 1.0 / (1.0 + e);
+          g += hb[r] * (x >= 0.0 ? s : e * s);
+          dg += hb[r] * (e * s * s);
+        }
+      }
+      sum2(it & 1, g, dg);
+      g /= tot;
+      dg *= a.beta / tot;                         // -dg/dc
+      if (g > target) lo = m; else hi = m;
+      const double mid = 0.5 * (lo + hi);
+      if (mid <= lo || mid >= hi) { m = mid; break; }
+      const double step = (g - target) / dg, nx = m + step;
+      if (fabs(step) * a.beta < 1e-9) { m = nx; break; }
+      m = nx > lo && nx < hi ? nx : mid;          // (false for an infinite or NaN step)
+    }
   }
   if (tid == 0) {
-    a.c_out[h] = tot > 0.0 ? (float)(0.5 * (lo + hi)) : __builtin_nanf("");
+    a.c_out[h] = tot > 0.0 ? (float)m : __builtin_nanf("");
     if (a.target_out != nullptr) a.target_out[h] = tot > 0.0 ? target : __builtin_nan("");
   }
 }
@@ -2339,7 +2458,8 @@ hipError_t launch_calib(const eta_calib_desc_t& cd, const void* q, const void* k
                reinterpret_cast<unsigned long long*>(st.density), cd.num_q_heads, cd.num_kv_heads,
                cd.seq_len, cd.num_bins, cd.beta, cd.lo,
                (float)((double)cd.num_bins / ((double)cd.hi - (double)cd.lo))};
-  dim3 grid(cd.num_q_heads, cd.num_seqs);
+  const int64_t nq = ((int64_t)cd.seq_len + kCalibQ - 1) / kCalibQ, z = (nq + 3) / 4;
+  dim3 grid(cd.num_q_heads, cd.num_seqs, (unsigned)z);
   return with_hook(hook, ETA_KERNEL_CALIB_ACCUMULATE, stream, [&] {
     if (cd.head_dim == 64) hipLaunchKernelGGL(calib_kernel<64>, grid, dim3(256), 0, stream, ca);
     if (cd.head_dim == 128) hipLaunchKernelGGL(calib_kernel<128>, grid, dim3(256), 0, stream, ca);
@@ -2352,7 +2472,7 @@ hipError_t launch_calib_solve(const eta_calib_desc_t& cd, const eta_calib_state_
                     reinterpret_cast<const unsigned long long*>(st.density), c_out, target_out,
                     cd.num_bins, (double)cd.beta, (double)cd.lo, (double)cd.hi};
   return with_hook(hook, ETA_KERNEL_CALIB_SOLVE, stream, [&] {
-    hipLaunchKernelGGL(calib_solve_kernel, dim3(cd.num_q_heads), dim3(256), 0, stream, sa);
+    hipLaunchKernelGGL(calib_solve_kernel, dim3(cd.num_q_heads), dim3(kSolveThreads), 0, stream, sa);
   });
 }
 

@@ -114,3 +114,41 @@ def test_constant_dynamic_threshold_is_recovered():
     lo, hi, nb = -6.0, 10.0, 4096
     _, _, c, _ = _gpu_calibrate(cs, beta=4.0, lo=lo, hi=hi, nb=nb)
     assert np.all(np.abs(c - np.array(tau0)) <= (hi - lo) / nb), c
+
+
+@pytest.mark.parametrize("T,N,Hq,Hkv,d,nb", [(1, 2, 2, 1, 64, 1), (15, 1, 2, 2, 128, 777),
+                                             (64, 1, 4, 1, 64, 4096), (65, 2, 2, 1, 128, 1000),
+                                             (256, 1, 2, 2, 128, 1024), (321, 1, 8, 1, 64, 1025)])
+def test_calibration_block_edges(T, N, Hq, Hkv, d, nb):
+    """Steps around the 16-query groups, 64-query blocks and 256-query workgroups; bins
+    around the solver's 1024 threads."""
+    CASES.append((N, Hq, Hkv, T, d, 4.0, -6.0, 10.0, nb))
+    try:
+        test_calibration_matches_oracle(len(CASES) - 1)
+    finally:
+        CASES.pop()
+
+
+def test_calibration_adds_up_over_calls_with_several_workgroups_per_head():
+    cs = calib_stream(N=5, Hq=4, Hkv=2, T=700, d=64, seed=17, device="cuda")
+    kw = dict(beta=4.0, lo=-8.0, hi=24.0, nb=1024)
+    a = _gpu_calibrate(cs, **kw)
+    for splits in (2, 5):
+        for x, y in zip(a, _gpu_calibrate(cs, splits=splits, **kw)):
+            assert np.array_equal(x, y)
+
+
+@pytest.mark.parametrize("tau", [-60.0, 60.0, 1e30])
+def test_saturated_gates_solve_to_the_end_of_the_bracket(tau):
+    """Every gate fully open or shut (1e30: the gate's exponential overflows): the
+    density is 1 or 0 and the solution runs to an end of the bracket, as in the oracle's
+    bisection of the same histogram and density."""
+    cs = calib_stream(N=1, Hq=2, Hkv=1, T=100, d=64, seed=5, tau_const=[tau, tau], device="cuda")
+    lo, hi, nb = -8.0, 24.0, 512
+    hist, dens, c, target = _gpu_calibrate(cs, beta=4.0, lo=lo, hi=hi, nb=nb)
+    for h in range(2):
+        assert abs(target[h] - (1.0 if tau < 0 else 0.0)) <= 1e-7
+        ref = oracle.calib_solve(hist[h] / eta.CALIB_UNIT, lo, hi, 4.0, float(target[h]))
+        g = [oracle.calib_g(hist[h] / eta.CALIB_UNIT, lo, hi, 4.0, float(v)) for v in (c[h], ref)]
+        # (where g is flat at fp64 precision, any point of the flat stretch solves it)
+        assert abs(g[0] - target[h]) <= abs(g[1] - target[h]) + 1e-12
