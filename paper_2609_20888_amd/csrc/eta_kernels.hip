@@ -1023,7 +1023,16 @@ __global__ __launch_bounds__(kScreenThreads) void screen_kernel(ScreenArgs a) {
 // it did not select even when a sibling head of the group loaded them (the
 // union is loaded once, each head keeps its own online-softmax state).  The
 // last split also attends the partial tail.  The four wavefront states are
-// merged through LDS into one partial (max, sum, acc) per head and split.
+// merged through LDS into one partial (max, sum, acc) per head and split, the
+// maximum in base-2 units.
+//
+// Bound by HBM at one to four heads of 128 dims; with eight heads of 64 by the
+// vector unit and latency (a 16 KB tile carries 1024 weights and 65536
+// multiply-adds of p.V): so the gate and softmax are branchless, base-2 and without
+// wavefront-wide steps in the usual tile, A's zeros come from LDS instead of under a
+// branch per chunk, and V of 64-dim rows is read two rows per load.  Split decode, 32
+// sequences of 64K, 32/4 heads, d = 64: 141 -> 107 us; 512K / 20%, d = 128: 101 ->
+// 98 us (step 110.9 -> 107.7); 8 x 128K step 89.6 -> 86.8 us.
 
 // bf16 V rows in the split kernels: each wavefront load reads whole rows (128
 // or 256 bytes), each read once per step, so they are loaded with the
@@ -1034,9 +1043,6 @@ __global__ __launch_bounds__(kScreenThreads) void screen_kernel(ScreenArgs a) {
 // 198 us).
 __device__ __forceinline__ uint32_t load_v_pair(const uint16_t* p) {
   return __builtin_nontemporal_load(reinterpret_cast<const uint32_t*>(p));
-}
-__device__ __forceinline__ uint16_t load_v_one(const uint16_t* p) {
-  return __builtin_nontemporal_load(p);
 }
 
 // Scores of bf16 K on the matrix cores: v_mfma_f32_16x16x32_bf16 with a
@@ -1082,299 +1088,313 @@ struct SplitArgs {
 namespace {
 
 
-// Gated score S~ = S sigmoid(beta (S - tau_eff)); -inf when the head does not
-// attend the token.
+// Gated score S~ = S sigmoid(beta (S - tau_eff)) in base-2 units (S log2 e, so that
+// exp(S~) = 2^x), from the product c = q.k: s2 = log2 e / sqrt(d), nbs = -beta s2, bt =
+// beta tau_eff log2 e (-inf: no gate).  -inf when the head does not attend the token.
+// Without branches: a head's chain runs beside the other heads'.
+constexpr float kLog2e = 1.4426950408889634f;
+
 template <bool DENSE>
-__device__ __forceinline__ float gated(float S, bool attend, bool ungated, float teff, float beta) {
-  if (!attend) return kNegInf;
-  if (DENSE || ungated || teff == kNegInf) return S;
-  return S * __builtin_amdgcn_rcpf(1.0f + __expf(-beta * (S - teff)));
+__device__ __forceinline__ float gated(float c, bool attend, bool ungated, float s2, float nbs, float bt) {
+  float x = c * s2;
+  if constexpr (!DENSE) {
+    const float sig = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(fmaf(nbs, c, bt)));
+    x *= ungated ? 1.0f : sig;
+  }
+  return attend ? x : kNegInf;
 }
 
-// Online-softmax update of one head with this lane's score `sc`; returns the
-// lane's weight and rescales the head's accumulator.
-template <int DPL>
-__device__ __forceinline__ float softmax_step(float sc, float& m, float& l, float (&acc)[DPL]) {
-  const float bm = wave_max(sc);
-  const float mn = fmaxf(m, bm);
-  if (mn == kNegInf) return 0.f;
-  const float alpha = __expf(m - mn);
-  const float p = __expf(sc - mn);
-  l = l * alpha + wave_sum(p);
-  m = mn;
+// Online softmax (base 2) of a wavefront's heads against a reference maximum m that
+// moves only when some lane's score passes it by more than 8, t = m + 8 (weights stay
+// below 2^8): the usual tile needs no wavefront-wide maximum, no rescaling and no
+// wavefront-wide sum (l is this lane's share of the sum; the lanes are added at the
+// end).  m and t are the same in every lane; before a head's first key m = 0 and
+// t = -inf.  Scores of keys a head does not attend are -inf and weigh 0.
+template <int G, int NA>
+struct SoftState {
+  float m[G], t[G], l[G], acc[G][NA];
+
+  __device__ __forceinline__ void init() {
 #pragma unroll
-  for (int e = 0; e < DPL; ++e) acc[e] *= alpha;
-  return p;
-}
+    for (int h = 0; h < G; ++h) {
+      m[h] = l[h] = 0.f;
+      t[h] = kNegInf;
+#pragma unroll
+      for (int e = 0; e < NA; ++e) acc[h][e] = 0.f;
+    }
+  }
 
-// fp32 K/V: scores on the vector ALUs.
+  // scores -> weights
+  __device__ __forceinline__ void step(const float (&sc)[G], float (&p)[G]) {
+    bool over = false;
+#pragma unroll
+    for (int h = 0; h < G; ++h) over |= sc[h] > t[h];
+    if (__ballot(over) != 0ull) {
+#pragma unroll
+      for (int h = 0; h < G; ++h) {
+        const float bm = wave_max(sc[h]);
+        const float mn = t[h] == kNegInf ? (bm == kNegInf ? 0.f : bm) : fmaxf(m[h], bm);
+        const float alpha = __builtin_amdgcn_exp2f(m[h] - mn);   // before the first key: times 0
+        m[h] = mn;
+        if (t[h] != kNegInf || bm != kNegInf) t[h] = mn + 8.0f;
+        l[h] = l[h] == 0.f ? 0.f : l[h] * alpha;
+#pragma unroll
+        for (int e = 0; e < NA; ++e) acc[h][e] = acc[h][e] == 0.f ? 0.f : acc[h][e] * alpha;
+      }
+    }
+#pragma unroll
+    for (int h = 0; h < G; ++h) {
+      p[h] = __builtin_amdgcn_exp2f(sc[h] - m[h]);
+      l[h] += p[h];
+    }
+  }
+
+  // the head's reference maximum, -inf when it attended nothing
+  __device__ __forceinline__ float max_of(int h) const { return t[h] == kNegInf ? kNegInf : m[h]; }
+};
+
+// fp32 K/V: scores on the vector ALUs.  A split of a short cache is one tile, all
+// latency: K and the first half of V are requested together, the rest of V two chunks
+// ahead (one 4K sequence, d = 64: split decode 7.8 -> 6.6 us; two 16K sequences, 32/8
+// heads, d = 128: step 51.8 -> 44.8 us).
 template <int D, int G, bool DENSE>
 __device__ __forceinline__ void attend_f32(const float* __restrict__ kb, const float* __restrict__ vb,
                                            int64_t st, int64_t t0, int nvalid, uint32_t bits,
-                                           const float (*qf_s)[G], const float* teff_s,
-                                           float (*p_s)[G], float beta, int64_t self_t, int lane,
-                                           float (&m_)[G], float (&l_)[G], float (&acc)[G][D / 64]) {
+                                           const float (*qf_s)[G], const float* bt_s,
+                                           float (*p_s)[G], float nbs, int64_t self_t, int lane,
+                                           SoftState<G, D / 64>& ss) {
   constexpr int DPL = D / 64;
+  constexpr int VC = 16;                   // tokens per V chunk, two chunks in flight
   for (int sb = 0; sb < nvalid; sb += 64) {
     asm volatile("" ::: "memory");
     const int nv = nvalid - sb < 64 ? nvalid - sb : 64;
     const bool valid = lane < nv;
     const int64_t row = t0 + sb + (valid ? lane : 0);
+    // the first V rows are requested with K's (rows past the valid ones read the
+    // tile's first row and get weight 0)
+    float vr[2][VC][DPL];
+    auto load_v = [&](int c) {
+#pragma unroll
+      for (int t = 0; t < VC; ++t) {
+        const int tt = VC * c + t;
+        Elem<float>::template loadn<DPL>(vb + (t0 + sb + (tt < nv ? tt : 0)) * st + lane * DPL, vr[c & 1][t]);
+      }
+    };
     float dot[G];
 #pragma unroll
     for (int h = 0; h < G; ++h) dot[h] = 0.f;
-#pragma unroll 2
-    for (int i = 0; i < D; i += 8) {
-      float x[8];
-      Elem<float>::load8(kb + row * st + i, x);
+    constexpr int KH = 64;                 // K elements in flight
+    float x[KH];
 #pragma unroll
-      for (int e = 0; e < 8; ++e)
+    for (int i0 = 0; i0 < D; i0 += KH) {
 #pragma unroll
-        for (int h = 0; h < G; ++h) dot[h] = fmaf(x[e], qf_s[i + e][h], dot[h]);
+      for (int i = 0; i < KH; i += 8) Elem<float>::load8(kb + row * st + i0 + i, *reinterpret_cast<float (*)[8]>(&x[i]));
+      if (i0 == 0) {
+        load_v(0);
+        load_v(1);
+      }
+#pragma unroll
+      for (int i = 0; i < KH; ++i)
+#pragma unroll
+        for (int h = 0; h < G; ++h) dot[h] = fmaf(x[i], qf_s[i0 + i][h], dot[h]);
     }
     const bool ung = (t0 + sb + lane) == self_t;
+    float sc[G], p[G];
 #pragma unroll
-    for (int h = 0; h < G; ++h) {
-      const float sc = gated<DENSE>(dot[h], valid && ((bits >> h) & 1u), ung, teff_s[h], beta);
-      p_s[lane][h] = softmax_step<DPL>(sc, m_[h], l_[h], acc[h]);
-    }
+    for (int h = 0; h < G; ++h)
+      sc[h] = gated<DENSE>(dot[h], valid && ((bits >> h) & 1u), ung, kLog2e, nbs, bt_s[h]);
+    ss.step(sc, p);
+#pragma unroll
+    for (int h = 0; h < G; ++h) p_s[lane][h] = p[h];
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
-    for (int t = 0; t < nv; ++t) {
-      float vv[DPL];
-      Elem<float>::template loadn<DPL>(vb + (t0 + sb + t) * st + lane * DPL, vv);
 #pragma unroll
-      for (int h = 0; h < G; ++h) {
-        const float ph = p_s[t][h];
+    for (int c = 0; c < 64 / VC; ++c) {
 #pragma unroll
-        for (int e = 0; e < DPL; ++e) acc[h][e] = fmaf(ph, vv[e], acc[h][e]);
-      }
+      for (int t = 0; t < VC; ++t)
+#pragma unroll
+        for (int h = 0; h < G; ++h) {
+          const float ph = p_s[VC * c + t][h];
+#pragma unroll
+          for (int e = 0; e < DPL; ++e) ss.acc[h][e] = fmaf(ph, vr[c & 1][t][e], ss.acc[h][e]);
+        }
+      if (c + 2 < 64 / VC) load_v(c + 2);
     }
     __builtin_amdgcn_wave_barrier();
   }
 }
 
-// bf16 K/V: scores on the matrix cores.
+// bf16 K/V, one 64-token tile of a wavefront: scores on the matrix cores, gate and
+// softmax, weights to LDS, p.V.  V is read in dwords (two dims per lane): a load
+// covers one row of 128 dims, or two rows of 64, so with D = 64 half a wavefront takes
+// the even tokens and half the odd ones and the halves are added at the end.
 template <int D, int G, bool DENSE>
-__device__ __forceinline__ void attend_bf16(const uint16_t* __restrict__ kb,
-                                            const uint16_t* __restrict__ vb, int64_t st, int64_t t0,
-                                            int nvalid, uint32_t bits, const bf16x8* qa_s,
-                                            bool use_lo, const float* teff_s, float* p_s,
-                                            float beta, float scale, int64_t self_t, int lane,
-                                            float (&m_)[G], float (&l_)[G],
-                                            float (&acc)[G][D / 64]) {
-  constexpr int DPL = D / 64;
-  constexpr int DC = D / 8;               // 16-byte chunks per row = MFMAs per head quad
-  constexpr int NQ = G > 4 ? G / 4 : 1;   // head quads
-  constexpr int GQ = 4 * NQ;              // padded heads (LDS row of p)
-  const bool diag = ((lane & 15) >> 2) == (lane >> 4);
-  const int qrow = lane & 3;
-  for (int sb = 0; sb < nvalid; sb += 64) {
-    asm volatile("" ::: "memory");
-    const int nv = nvalid - sb < 64 ? nvalid - sb : 64;
-    const bool valid = lane < nv;
-    const int64_t tb = t0 + sb;
-    // issue every load of the 64-token step first: this lane's K row and, for
-    // every token, this lane's head-dimension pair of V (rows past the valid
-    // ones read token tb again and get weight 0)
-    uint4 kr[DC];
-    const uint16_t* krow = kb + (tb + (valid ? lane : 0)) * st;
-#pragma unroll
-    for (int c = 0; c < DC; ++c) kr[c] = *reinterpret_cast<const uint4*>(krow + 8 * c);
-    uint32_t vr[64];
-#pragma unroll
-    for (int t = 0; t < 64; ++t) {
-      const int64_t r = tb + (t < nv ? t : 0);
-      if constexpr (DPL == 2)
-        vr[t] = load_v_pair(vb + r * st + 2 * lane);
-      else
-        vr[t] = load_v_one(vb + r * st + lane);
-    }
-    const bool ung = (tb + lane) == self_t;
-#pragma unroll
-    for (int hq = 0; hq < NQ; ++hq) {
-      f32x4 c = {0.f, 0.f, 0.f, 0.f};
-      const bf16x8 zero = {};
-#pragma unroll
-      for (int ch = 0; ch < DC; ++ch) {
-        const bf16x8 bk = __builtin_bit_cast(bf16x8, kr[ch]);
-        const bf16x8 ahi = diag ? qa_s[((hq * 2 + 0) * 4 + qrow) * DC + ch] : zero;
-        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ahi, bk, c, 0, 0, 0);
-        if (use_lo) {
-          const bf16x8 alo = diag ? qa_s[((hq * 2 + 1) * 4 + qrow) * DC + ch] : zero;
-          c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(alo, bk, c, 0, 0, 0);
-        }
-      }
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int h = 4 * hq + r;
-        if (h < G) {
-          const float sc =
-              gated<DENSE>(c[r] * scale, valid && ((bits >> h) & 1u), ung, teff_s[h], beta);
-          p_s[lane * GQ + h] = softmax_step<DPL>(sc, m_[h], l_[h], acc[h]);
-        }
-      }
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-    for (int t = 0; t < 64; ++t) {
-      float vv[DPL];
-      if constexpr (DPL == 2) {
-        vv[0] = bf16lo(vr[t]);
-        vv[1] = bf16hi(vr[t]);
-      } else {
-        vv[0] = bf16lo(vr[t]);
-      }
-#pragma unroll
-      for (int hq = 0; hq < NQ; ++hq) {
-        const float4 p4 = *reinterpret_cast<const float4*>(p_s + t * GQ + 4 * hq);
-        const float pr[4] = {p4.x, p4.y, p4.z, p4.w};
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int h = 4 * hq + r;
-          if (h < G) {
-#pragma unroll
-            for (int e = 0; e < DPL; ++e) acc[h][e] = fmaf(pr[r], vv[e], acc[h][e]);
-          }
-        }
-      }
-    }
-    __builtin_amdgcn_wave_barrier();
-  }
-}
+struct Bf16Tile {
+  static constexpr int DC = D / 8;               // 16-byte chunks per row = MFMAs per head quad
+  static constexpr int NQ = G > 4 ? G / 4 : 1;   // head quads
+  static constexpr int GQ = 4 * NQ;              // padded heads (LDS row of p)
+  static constexpr int TPL = 128 / D;            // tokens per V load
+  static constexpr int NV = 64 / TPL;            // V loads per tile
 
-// bf16 K/V, full 64-token tiles of one wavefront, software-pipelined: the next
-// tile's K loads are issued as soon as this tile's MFMAs have consumed the K
-// registers, and its V loads as soon as p.V has consumed the V registers, so
-// each wavefront keeps about one tile of K and V in flight while it computes.
-// tile_base(u) gives the first token of tile u, tile_bits(u) its head mask.
-template <int D, int G, bool DENSE, typename TB, typename BITS>
-__device__ __forceinline__ void attend_bf16_stream(const uint16_t* __restrict__ kb,
-                                                   const uint16_t* __restrict__ vb, int64_t st,
-                                                   int ntiles, TB tile_base, BITS tile_bits,
-                                                   const bf16x8* qa_s, bool use_lo,
-                                                   const float* teff_s, float* p_s, float beta,
-                                                   float scale, int64_t self_t, int lane,
-                                                   float (&m_)[G], float (&l_)[G],
-                                                   float (&acc)[G][D / 64]) {
-  constexpr int DPL = D / 64;
-  constexpr int DC = D / 8;
-  constexpr int NQ = G > 4 ? G / 4 : 1;
-  constexpr int GQ = 4 * NQ;
-  if (ntiles <= 0) return;
-  const bool diag = ((lane & 15) >> 2) == (lane >> 4);
-  const int qrow = lane & 3;
-  uint4 kr[DC];
-  uint32_t vr[64];
-  auto load_k = [&](int64_t tb) {
-    const uint16_t* krow = kb + (tb + lane) * st;
-#pragma unroll
-    for (int c = 0; c < DC; ++c) kr[c] = *reinterpret_cast<const uint4*>(krow + 8 * c);
-  };
-  auto load_v_rows = [&](int64_t tb, int t0) {
-#pragma unroll
-    for (int t = t0; t < t0 + 16; ++t) {
-      if constexpr (DPL == 2)
-        vr[t] = load_v_pair(vb + (tb + t) * st + 2 * lane);
-      else
-        vr[t] = load_v_one(vb + (tb + t) * st + lane);
-    }
-  };
-  auto load_v = [&](int64_t tb) {
-#pragma unroll
-    for (int qt = 0; qt < 4; ++qt) load_v_rows(tb, 16 * qt);
-  };
-  // One tile: scores on the MFMAs, then (MORE) the next tile's K loads into the
-  // freed K registers, the softmax update, p.V, then (MORE) the next tile's V
-  // loads.  The last tile is peeled (MORE = false) so that the loads inside the
-  // loop are unconditional: a conditional reload would keep two copies of the
-  // K/V registers alive across the branch.
-  auto tile = [&](int u, int64_t tb, int64_t tbn, auto more_tag) {
-    constexpr bool MORE = decltype(more_tag)::value;
-    asm volatile("" ::: "memory");
-    const uint32_t bits = tile_bits(u);
-    const bool ung = (tb + lane) == self_t;
-    f32x4 c[NQ];
+  const uint16_t* kb;
+  const uint16_t* vb;
+  int64_t st;
+  const bf16x8* qa;      // this lane's A operands: (quad, part) at (2 quad + part) 4 DC, zeros off the diagonal
+  bool use_lo;
+  const float* bt_s;
+  float* p_s;
+  float s2, nbs;
+  int64_t self_t;
+  int lane;
+
+  __device__ __forceinline__ int tok(int t) const { return TPL == 1 ? t : 2 * t + (lane >> 5); }
+  __device__ __forceinline__ int vcol() const { return TPL == 1 ? 2 * lane : 2 * (lane & 31); }
+
+  // scores of this lane's token (its K row in kr) for the G heads
+  __device__ __forceinline__ void dots(const uint4 (&kr)[DC], f32x4 (&c)[NQ]) const {
 #pragma unroll
     for (int hq = 0; hq < NQ; ++hq) {
       c[hq] = f32x4{0.f, 0.f, 0.f, 0.f};
-      const bf16x8 zero = {};
 #pragma unroll
-      for (int ch = 0; ch < DC; ++ch) {
-        const bf16x8 bk = __builtin_bit_cast(bf16x8, kr[ch]);
-        const bf16x8 ahi = diag ? qa_s[((hq * 2 + 0) * 4 + qrow) * DC + ch] : zero;
-        c[hq] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ahi, bk, c[hq], 0, 0, 0);
-        if (use_lo) {
-          const bf16x8 alo = diag ? qa_s[((hq * 2 + 1) * 4 + qrow) * DC + ch] : zero;
-          c[hq] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(alo, bk, c[hq], 0, 0, 0);
-        }
+      for (int ch = 0; ch < DC; ++ch)
+        c[hq] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qa[2 * hq * 4 * DC + ch], __builtin_bit_cast(bf16x8, kr[ch]),
+                                                         c[hq], 0, 0, 0);
+      if (use_lo) {
+#pragma unroll
+        for (int ch = 0; ch < DC; ++ch)
+          c[hq] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qa[(2 * hq + 1) * 4 * DC + ch],
+                                                           __builtin_bit_cast(bf16x8, kr[ch]), c[hq], 0, 0, 0);
       }
     }
-    if constexpr (MORE) {
-      __builtin_amdgcn_sched_barrier(0);
-      load_k(tbn);
-      __builtin_amdgcn_sched_barrier(0);
-    }
+  }
+
+  // gate, softmax; the tile's weights to LDS
+  __device__ __forceinline__ void weights(const f32x4 (&c)[NQ], bool valid, uint32_t bits, bool ung,
+                                          SoftState<G, 2>& ss) const {
+    float sc[G], pg[G], p[GQ];
+#pragma unroll
+    for (int h = 0; h < G; ++h)
+      sc[h] = gated<DENSE>(c[h / 4][h % 4], valid && ((bits >> h) & 1u), ung, s2, nbs, bt_s[h]);
+    ss.step(sc, pg);
+#pragma unroll
+    for (int h = 0; h < GQ; ++h) p[h] = h < G ? pg[h < G ? h : 0] : 0.f;
+#pragma unroll
+    for (int hq = 0; hq < NQ; ++hq)
+      *reinterpret_cast<float4*>(p_s + lane * GQ + 4 * hq) =
+          make_float4(p[4 * hq], p[4 * hq + 1], p[4 * hq + 2], p[4 * hq + 3]);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  }
+
+  // p.V of V load t
+  __device__ __forceinline__ void pv(int t, uint32_t v, SoftState<G, 2>& ss) const {
+    const float v0 = bf16lo(v), v1 = bf16hi(v);
 #pragma unroll
     for (int hq = 0; hq < NQ; ++hq) {
+      const float4 p4 = *reinterpret_cast<const float4*>(p_s + tok(t) * GQ + 4 * hq);
+      const float pr[4] = {p4.x, p4.y, p4.z, p4.w};
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int h = 4 * hq + r;
         if (h < G) {
-          const float sc = gated<DENSE>(c[hq][r] * scale, (bits >> h) & 1u, ung, teff_s[h], beta);
-          p_s[lane * GQ + h] = softmax_step<DPL>(sc, m_[h], l_[h], acc[h]);
+          ss.acc[h][0] = fmaf(pr[r], v0, ss.acc[h][0]);
+          ss.acc[h][1] = fmaf(pr[r], v1, ss.acc[h][1]);
         }
       }
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    // p.V in four quarters of 16 tokens; as soon as a quarter's V registers
-    // are consumed, that quarter of the next tile's V rows is requested, so
-    // those loads overlap the rest of this tile and the next tile's scores
+  }
+
+  // nvalid (any number) consecutive tokens from t0
+  __device__ __forceinline__ void attend(int64_t t0, int nvalid, uint32_t bits, SoftState<G, 2>& ss) const {
+    for (int sb = 0; sb < nvalid; sb += 64) {
+      asm volatile("" ::: "memory");
+      const int nv = nvalid - sb < 64 ? nvalid - sb : 64;
+      const bool valid = lane < nv;
+      const int64_t tb = t0 + sb;
+      // every load of the step first: this lane's K row and its part of V (rows past
+      // the valid ones read token tb again and get weight 0)
+      uint4 kr[DC];
+      const uint16_t* krow = kb + (tb + (valid ? lane : 0)) * st;
 #pragma unroll
-    for (int qt = 0; qt < 4; ++qt) {
+      for (int c = 0; c < DC; ++c) kr[c] = *reinterpret_cast<const uint4*>(krow + 8 * c);
+      uint32_t vr[NV];
 #pragma unroll
-      for (int t = 16 * qt; t < 16 * qt + 16; ++t) {
-        float vv[DPL];
-        if constexpr (DPL == 2) {
-          vv[0] = bf16lo(vr[t]);
-          vv[1] = bf16hi(vr[t]);
-        } else {
-          vv[0] = bf16lo(vr[t]);
-        }
+      for (int t = 0; t < NV; ++t)
+        vr[t] = load_v_pair(vb + (tb + (tok(t) < nv ? tok(t) : 0)) * st + vcol());
+      f32x4 c[NQ];
+      dots(kr, c);
+      weights(c, valid, bits, (tb + lane) == self_t, ss);
 #pragma unroll
-        for (int hq = 0; hq < NQ; ++hq) {
-          const float4 p4 = *reinterpret_cast<const float4*>(p_s + t * GQ + 4 * hq);
-          const float pr[4] = {p4.x, p4.y, p4.z, p4.w};
+      for (int t = 0; t < NV; ++t) pv(t, vr[t], ss);
+      __builtin_amdgcn_wave_barrier();
+    }
+  }
+
+  // Full 64-token tiles of one wavefront, software-pipelined: the next tile's K loads
+  // are issued as soon as this tile's MFMAs have consumed the K registers, and its V
+  // loads as soon as p.V has consumed the V registers, so each wavefront keeps about
+  // one tile of K and V in flight while it computes.  tile_base(u) gives the first
+  // token of tile u, tile_bits(u) its head mask.
+  template <typename TB, typename BITS>
+  __device__ __forceinline__ void stream(int ntiles, TB tile_base, BITS tile_bits, SoftState<G, 2>& ss) const {
+    if (ntiles <= 0) return;
+    constexpr int NR = NV / 4;                   // V loads per quarter of the tile
+    uint4 kr[DC];
+    uint32_t vr[NV];
+    auto load_k = [&](int64_t tb) {
+      const uint16_t* krow = kb + (tb + lane) * st;
 #pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const int h = 4 * hq + r;
-            if (h < G) {
+      for (int c = 0; c < DC; ++c) kr[c] = *reinterpret_cast<const uint4*>(krow + 8 * c);
+    };
+    // (the lane's part of the address first, then wave-uniform steps of whole rows)
+    const uint16_t* vl = vb + (TPL == 1 ? 0 : (lane >> 5) * st) + vcol();
+    auto load_v_rows = [&](int64_t tb, int t0) {
+      const uint16_t* vt = vl + tb * st;
 #pragma unroll
-              for (int e = 0; e < DPL; ++e) acc[h][e] = fmaf(pr[r], vv[e], acc[h][e]);
-            }
-          }
-        }
-      }
+      for (int t = t0; t < t0 + NR; ++t) vr[t] = load_v_pair(vt + TPL * t * st);
+    };
+    // One tile: scores on the MFMAs, then (MORE) the next tile's K loads into the
+    // freed K registers, the softmax update, p.V in four quarters, each followed by
+    // (MORE) that quarter of the next tile's V loads.  The last tile is peeled
+    // (MORE = false) so that the loads inside the loop are unconditional: a
+    // conditional reload would keep two copies of the K/V registers alive across
+    // the branch.
+    auto tile = [&](int u, int64_t tb, int64_t tbn, auto more_tag) {
+      constexpr bool MORE = decltype(more_tag)::value;
+      asm volatile("" ::: "memory");
+      const uint32_t bits = __builtin_amdgcn_readfirstlane(tile_bits(u));
+      f32x4 c[NQ];
+      dots(kr, c);
       if constexpr (MORE) {
         __builtin_amdgcn_sched_barrier(0);
-        load_v_rows(tbn, 16 * qt);
+        load_k(tbn);
         __builtin_amdgcn_sched_barrier(0);
       }
+      weights(c, true, bits, (tb + lane) == self_t, ss);
+#pragma unroll
+      for (int qt = 0; qt < 4; ++qt) {
+#pragma unroll
+        for (int t = NR * qt; t < NR * (qt + 1); ++t) pv(t, vr[t], ss);
+        if constexpr (MORE) {
+          __builtin_amdgcn_sched_barrier(0);
+          load_v_rows(tbn, NR * qt);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+      __builtin_amdgcn_wave_barrier();
+    };
+    int64_t tb = tile_base(0);
+    load_k(tb);
+#pragma unroll
+    for (int qt = 0; qt < 4; ++qt) load_v_rows(tb, NR * qt);
+    for (int u = 0; u + 1 < ntiles; ++u) {
+      const int64_t tbn = tile_base(u + 1);
+      tile(u, tb, tbn, std::integral_constant<bool, true>{});
+      tb = tbn;
     }
-    __builtin_amdgcn_wave_barrier();
-  };
-  int64_t tb = tile_base(0);
-  load_k(tb);
-  load_v(tb);
-  for (int u = 0; u + 1 < ntiles; ++u) {
-    const int64_t tbn = tile_base(u + 1);
-    tile(u, tb, tbn, std::integral_constant<bool, true>{});
-    tb = tbn;
+    tile(ntiles - 1, tb, tb, std::integral_constant<bool, false>{});
   }
-  tile(ntiles - 1, tb, tb, std::integral_constant<bool, false>{});
-}
+};
 
 constexpr int kItemChunk = 256;
 // Wavefronts per split-decode workgroup.
@@ -1383,8 +1403,8 @@ constexpr int kSplitWaves = 4;
 template <int D, int BS, int G, typename KVT, bool DENSE, bool PROP>
 __global__ __launch_bounds__(64 * kSplitWaves) void split_kernel(SplitArgs a) {
   constexpr int NW = kSplitWaves, NT = 64 * NW;
-  constexpr int DPL = D / 64;
   constexpr bool BF = sizeof(KVT) == 2;
+  constexpr int NA = BF ? 2 : D / 64;      // head dimensions per lane
   constexpr int NQ = G > 4 ? G / 4 : 1;
   constexpr int GQ = 4 * NQ;
   constexpr int DC = D / 8;
@@ -1392,11 +1412,12 @@ __global__ __launch_bounds__(64 * kSplitWaves) void split_kernel(SplitArgs a) {
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
   __shared__ float qf_s[BF ? 1 : D][G];                  // fp32 path: scaled q
   __shared__ bf16x8 qa_s[BF ? NQ * 2 * 4 * DC : 1];      // bf16 path: q chunks (hi, lo)
-  __shared__ float teff_s[G];
+  __shared__ bf16x8 qz_s[BF ? (2 * NQ - 1) * 4 * DC + DC : 1];  // zeros, read off A's diagonal
+  __shared__ float bt_s[G];
   __shared__ int pref_s[kMaxTiles + 1];
   __shared__ int wsum_s[NW];
   __shared__ float mrg_ml[NW][G][2];
-  __shared__ float mrg_acc[NW][G][D];
+  __shared__ __attribute__((aligned(8))) float mrg_acc[NW][G][D];
   __shared__ __attribute__((aligned(16))) float p_s[NW][64 * GQ];
   __shared__ int32_t item_j[kItemChunk];
   __shared__ uint8_t item_bits[kItemChunk];
@@ -1616,7 +1637,13 @@ __global__ __launch_bounds__(64 * kSplitWaves) void split_kernel(SplitArgs a) {
       }
     }
   }
-  if (tid < G) teff_s[tid] = DENSE ? 0.f : tau_in - a.offset_a;
+  if constexpr (BF) {
+    for (int idx = tid; idx < (2 * NQ - 1) * 4 * DC + DC; idx += NT) qz_s[idx] = bf16x8{};
+  }
+  if (tid < G) {
+    const float teff = tau_in - a.offset_a;
+    bt_s[tid] = DENSE || teff == kNegInf ? kNegInf : a.beta * teff * kLog2e;
+  }
   for (int idx = tid; idx < NW * 64 * GQ; idx += NT) (&p_s[0][0])[idx] = 0.f;
 
   // The split's share of the list (the union's blocks, or every block when
@@ -1714,22 +1741,21 @@ __global__ __launch_bounds__(64 * kSplitWaves) void split_kernel(SplitArgs a) {
   const KVT* vb = reinterpret_cast<const KVT*>(a.v) + (int64_t)b * g.sb + (int64_t)gh * g.sh;
   const int64_t self_t = (!DENSE && a.self_ungated) ? T - 1 : -1;
   const bool use_lo = a.q_dtype == ETA_DT_F32;
-  float m_[G], l_[G], acc[G][DPL];
-#pragma unroll
-  for (int h = 0; h < G; ++h) {
-    m_[h] = kNegInf;
-    l_[h] = 0.f;
-#pragma unroll
-    for (int e = 0; e < DPL; ++e) acc[h][e] = 0.f;
-  }
+  SoftState<G, NA> ss;
+  ss.init();
+  // row 4 tg + h of A holds query head h in the k-slots of lane group tg: lanes of
+  // other groups read zeros
+  const bool diag = ((lane & 15) >> 2) == (lane >> 4);
+  [[maybe_unused]] const Bf16Tile<D, G, DENSE> bt{
+      reinterpret_cast<const uint16_t*>(kb), reinterpret_cast<const uint16_t*>(vb), g.st,
+      diag ? qa_s + (lane & 3) * DC : qz_s, use_lo, bt_s, p_s[w], scale * kLog2e,
+      -a.beta * (scale * kLog2e), self_t, lane};
   auto attend = [&](int64_t t0, int nvalid, uint32_t bits) {
     if constexpr (BF)
-      attend_bf16<D, G, DENSE>(kb, vb, g.st, t0, nvalid, bits, qa_s, use_lo, teff_s, p_s[w],
-                               a.beta, scale, self_t, lane, m_, l_, acc);
+      bt.attend(t0, nvalid, bits, ss);
     else
-      attend_f32<D, G, DENSE>(kb, vb, g.st, t0, nvalid, bits, qf_s,
-                              teff_s, reinterpret_cast<float (*)[G]>(p_s[w]), a.beta, self_t, lane,
-                              m_, l_, acc);
+      attend_f32<D, G, DENSE>(kb, vb, g.st, t0, nvalid, bits, qf_s, bt_s,
+                              reinterpret_cast<float (*)[G]>(p_s[w]), -a.beta * kLog2e, self_t, lane, ss);
   };
   constexpr uint32_t all_bits = (1u << G) - 1u;
   // The split's items are resolved (union slot -> block id -> head bits) in
@@ -1765,14 +1791,13 @@ __global__ __launch_bounds__(64 * kSplitWaves) void split_kernel(SplitArgs a) {
       }
       __syncthreads();
       const int nmine = n > w ? (n - w + NW - 1) / NW : 0;
-      attend_bf16_stream<D, G, DENSE>(
-          kb, vb, g.st, nmine,
+      bt.stream(
+          nmine,
           [&](int u) {
             const int x = w + NW * u;
             return (int64_t)item_j[x] * BS + 64 * item_sub[x];
           },
-          [&](int u) { return (uint32_t)item_bits[w + NW * u]; }, qa_s, use_lo, teff_s, p_s[w],
-          a.beta, scale, self_t, lane, m_, l_, acc);
+          [&](int u) { return (uint32_t)item_bits[w + NW * u]; }, ss);
       __syncthreads();
     }
   } else {
@@ -1811,14 +1836,29 @@ __global__ __launch_bounds__(64 * kSplitWaves) void split_kernel(SplitArgs a) {
   if (s == S - 1 && ntail > 0 && w == NW - 1) attend(N * BS, ntail, all_bits);
 
   // merge the four wavefront states
+#pragma unroll
+  for (int h = 0; h < G; ++h) ss.l[h] = wave_sum(ss.l[h]);   // the lanes' shares of the weight sums
   if (lane == 0) {
 #pragma unroll
-    for (int h = 0; h < G; ++h) { mrg_ml[w][h][0] = m_[h]; mrg_ml[w][h][1] = l_[h]; }
+    for (int h = 0; h < G; ++h) { mrg_ml[w][h][0] = ss.max_of(h); mrg_ml[w][h][1] = ss.l[h]; }
   }
+  if constexpr (BF && D == 64) {
+    // lanes l and l + 32 hold the even and odd tokens' sums of dims 2 l, 2 l + 1
 #pragma unroll
-  for (int h = 0; h < G; ++h)
+    for (int h = 0; h < G; ++h) {
 #pragma unroll
-    for (int e = 0; e < DPL; ++e) mrg_acc[w][h][lane * DPL + e] = acc[h][e];
+      for (int e = 0; e < 2; ++e) {
+        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(ss.acc[h][e]), __float_as_uint(ss.acc[h][e]), false, false);
+        ss.acc[h][e] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+      }
+      if (lane < 32) *reinterpret_cast<float2*>(&mrg_acc[w][h][2 * lane]) = make_float2(ss.acc[h][0], ss.acc[h][1]);
+    }
+  } else {
+#pragma unroll
+    for (int h = 0; h < G; ++h)
+#pragma unroll
+      for (int e = 0; e < NA; ++e) mrg_acc[w][h][lane * NA + e] = ss.acc[h][e];
+  }
   __syncthreads();
   for (int idx = tid; idx < G * D; idx += NT) {
     const int h = idx / D, i = idx % D;
@@ -1831,7 +1871,7 @@ __global__ __launch_bounds__(64 * kSplitWaves) void split_kernel(SplitArgs a) {
       for (int k = 0; k < NW; ++k) {
         const float mk = mrg_ml[k][h][0];
         if (mk == kNegInf) continue;
-        const float wk = __expf(mk - ms);
+        const float wk = __builtin_amdgcn_exp2f(mk - ms);
         L = fmaf(mrg_ml[k][h][1], wk, L);
         o = fmaf(mrg_acc[k][h][i], wk, o);
       }
@@ -2235,14 +2275,14 @@ __global__ __launch_bounds__(kCombThreads) void combine_kernel(CombineArgs a) {
   if (ms != kNegInf) {
 #pragma unroll
     for (int k = 0; k < kCombPrefetch; ++k) {
-      const float wk = mv[k].x == kNegInf ? 0.f : __expf(mv[k].x - ms);
+      const float wk = mv[k].x == kNegInf ? 0.f : __builtin_amdgcn_exp2f(mv[k].x - ms);
       o = fmaf(wk, av[k], o);
       L = fmaf(mv[k].y, wk, L);
     }
 #pragma unroll 8
     for (int sidx = part + P * kCombPrefetch; sidx < S; sidx += P) {
       const float2 e = ml[sidx * st];
-      const float wk = e.x == kNegInf ? 0.f : __expf(e.x - ms);
+      const float wk = e.x == kNegInf ? 0.f : __builtin_amdgcn_exp2f(e.x - ms);
       o = fmaf(wk, accp[sidx * st * D], o);
       L = fmaf(e.y, wk, L);
     }

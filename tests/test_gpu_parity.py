@@ -168,6 +168,30 @@ def test_decode_matches_oracle(name):
     say(f"[gpu] {name}: {stats}")
 
 
+@pytest.mark.parametrize("dt", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("G,tail,beta", [(1, 1, 4.0), (2, 31, 0.0), (4, 33, 4.0), (8, 63, 1.0)])
+def test_decode_moving_reference_and_tails(G, d, dt, tail, beta):
+    """Scores that grow along the context (keys scaled up block by block along the
+    query), so the softmax reference has to move again and again and heads of a group
+    move at different tiles; odd tails; no gate slope (beta 0); heads that attend
+    nothing but the tail."""
+    Hkv, blk, n = 2, 64, 12
+    wl = make_workload(B=2, Hq=G * Hkv, Hkv=Hkv, d=d, block=blk, seq_lens=[n * blk + tail, tail],
+                       dtype=dt, predictor=False, tau_const=0.5, beta=beta, rescue_window=0,
+                       seed=300 + 10 * G + tail)
+    u = wl.q.float()[:, ::G] / wl.q.float()[:, ::G].norm(dim=-1, keepdim=True)    # [B][Hkv][d]
+    ramp = torch.arange(n * blk + tail) // blk * (60.0 / n)
+    wl.k = (wl.k.float() + ramp[None, None, :, None] * u[:, :, None]).to(dt)
+    if G > 1:
+        wl.bias[1] = 1e6               # selects no block: the tail alone
+    np_in = oracle_inputs(wl)
+    for splits in (0, 1, 3):
+        g = run_gpu(wl, num_splits=splits)
+        orc, tau_o = run_oracle(wl, np_in)
+        say(compare(wl, g, orc, tau_o, np_inputs=np_in, union_counts=g.union_counts))
+
+
 def test_decode_fp32_query_on_bf16_cache():
     # fp32 q with bf16 K/V: the scores use the hi + lo bf16 split of q
     wl = make_workload(B=1, Hq=8, Hkv=2, d=128, block=64, seq_lens=[9000],
