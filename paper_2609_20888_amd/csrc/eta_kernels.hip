@@ -244,7 +244,7 @@ __device__ __forceinline__ int wave_incl_scan(int x) {
 
 // ---------------------------------------------------------------- summaries
 //
-// One workgroup handles kSumBlocks consecutive full blocks of one (sequence,
+// One workgroup handles NB consecutive full blocks of one (sequence,
 // kv head); wavefront w takes blocks w, w + 4, ...  A block is read with
 // fully coalesced 16-byte loads: LPR lanes cover one row, so one load covers
 // R = 64 / LPR consecutive rows, and lane l keeps the EPL coordinates
@@ -252,15 +252,17 @@ __device__ __forceinline__ int wave_incl_scan(int x) {
 // stays in registers for the two passes (mean, then mean squared deviation);
 // the row norms are summed over the LPR lanes of a row, and the per-lane
 // sums over the R row groups.  Results are staged in LDS and written as whole
-// rows of kSumBlocks consecutive blocks of the dimension-major output.
+// rows of NB consecutive blocks of the dimension-major output.
 //
 // Variants: ENV replaces sigma by the sub-block envelope (per coordinate, the
 // largest root mean squared deviation from the block mean over contiguous
 // sub-blocks of 2^sub_log2 tokens); with prev_lens, the blocks start at
 // prev_lens[b] / BS (the blocks completed since then) and at most max_new
-// blocks per sequence are written.
-
-constexpr int kSumBlocks = 32;
+// blocks per sequence are written.  Its extra cost is the sums over each sub-block's row
+// groups: taken for two coordinates per row swap (32 x 64K tokens, 4 heads, d = 64, b = 64,
+// sub-blocks of 4: 290 -> 223 us; of 8: 320 -> 220).
+//
+// NB: 32 for large caches, else 4 (see launch_summaries).
 
 // Sum over the aligned group of N lanes (N in 8, 16, 32) that holds one row;
 // every lane of the group ends with the same value.
@@ -334,7 +336,7 @@ __device__ __forceinline__ void unpack16(const uint4& u, float (&f)[16 / sizeof(
   }
 }
 
-template <int D, int BS, typename KVT, bool ENV>
+template <int D, int BS, typename KVT, bool ENV, int NB>
 __global__ __launch_bounds__(256) void summaries_kernel(const KVT* __restrict__ k, Geom g,
                                                         const int32_t* __restrict__ seq_lens,
                                                         const int32_t* __restrict__ prev_lens,
@@ -349,20 +351,21 @@ __global__ __launch_bounds__(256) void summaries_kernel(const KVT* __restrict__ 
   constexpr int CH = NI * 4 <= 128 ? NI : 16;  // loads held at once (VGPR budget)
   constexpr int NCH = NI / CH;
   static_assert(LPR >= 8 && LPR <= 32 && NI % CH == 0, "unsupported summary shape");
-  // the envelope's sub-block sums over four row groups of 16 lanes (bf16 rows
-  // of 128) take the transposed route below when a sub-block spans all four
-  constexpr bool TR = ENV && LPR == 16 && EPL == 8;
-  const bool tr_on = TR && (1 << sub_log2) >= R;
-  __shared__ float mu_s[D][kSumBlocks + 1];
-  __shared__ float sg_s[D][kSumBlocks + 1];
-  __shared__ float mx_s[kSumBlocks];
+  // the envelope's sub-block sums over at least four row groups (bf16 rows: all
+  // four groups of 16 lanes at d = 128, four or eight of 8 lanes at d = 64) take the
+  // transposed route below
+  constexpr bool TR = ENV && EPL == 8;
+  const bool tr_on = TR && (1 << sub_log2) >= 4;
+  __shared__ float mu_s[D][NB + 1];
+  __shared__ float sg_s[D][NB + 1];
+  __shared__ float mx_s[NB];
 
   const int gh = blockIdx.y, b = blockIdx.z, tid = threadIdx.x;
   const int lane = tid & 63, w = tid >> 6;
   const int rg = lane / LPR, cl = lane % LPR;
   const int64_t T = clamp_len(seq_lens, b, g.cap);
   int64_t N = T / BS;
-  int64_t j0 = (int64_t)blockIdx.x * kSumBlocks;
+  int64_t j0 = (int64_t)blockIdx.x * NB;
   if (prev_lens != nullptr) {
     const int64_t first = clamp_len(prev_lens, b, g.cap) / BS;
     j0 += first;
@@ -373,7 +376,7 @@ __global__ __launch_bounds__(256) void summaries_kernel(const KVT* __restrict__ 
   const int64_t bg = (int64_t)b * g.Hkv + gh;
   constexpr float inv_bs = 1.0f / BS;
 
-  for (int jj = w; jj < kSumBlocks; jj += 4) {
+  for (int jj = w; jj < NB; jj += 4) {
     const int64_t j = j0 + jj;
     if (j >= N) break;
     const KVT* base = kb + (j * BS + rg) * g.st + cl * EPL;
@@ -410,7 +413,7 @@ __global__ __launch_bounds__(256) void summaries_kernel(const KVT* __restrict__ 
       mean[e] = row_group_reduce<LPR>(s[e], [](float a, float c) { return a + c; }) * inv_bs;
       s[e] = 0.f;   // pass two keeps the envelope here
     }
-    float tr_s[2] = {0.f, 0.f};
+    float tr_s[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int c = 0; c < NCH; ++c) {
       if constexpr (NCH > 1) {
@@ -435,23 +438,34 @@ __global__ __launch_bounds__(256) void summaries_kernel(const KVT* __restrict__ 
           const int ng = sub < R ? sub : R, kl = sub > R ? sub / R : 1;
           if (((c * CH + i + 1) & (kl - 1)) == 0) {
             const float inv_sub = 1.0f / (float)sub;
-            if (TR && ng == 4) {
-              // the eight coordinates' sums over the four row groups at once:
-              // each row swap exchanges two coordinates' rows, so the pairwise
-              // adds are those of partial_group_sum (same operands, same
-              // order) and coordinate 4 m + r ends in row r of tr_s[m]
+            if (TR && ng >= 4) {
+              // the eight coordinates' sums over the row groups at once: each row
+              // swap exchanges two coordinates' rows, so the pairwise adds are those
+              // of partial_group_sum (same operands, same order).  Over all rows
+              // (four groups of 16 lanes, eight of 8) coordinate 4 m + r ends in row r
+              // of tr_s[m]; over four groups of 8 lanes coordinate 2 p + r % 2 of the
+              // sub-block of rows r, r ^ 1 ends in row r of tr_s[p]
               float u[4];
 #pragma unroll
               for (int p = 0; p < 4; ++p) {
+                if constexpr (LPR == 8) {
+                  v[2 * p] += dpp_mov<0x128>(v[2 * p]);
+                  v[2 * p + 1] += dpp_mov<0x128>(v[2 * p + 1]);
+                }
                 const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v[2 * p]),
                                                                 __float_as_uint(v[2 * p + 1]), false, false);
                 u[p] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
               }
+              if (ng == R) {
 #pragma unroll
-              for (int m = 0; m < 2; ++m) {
-                const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(u[2 * m]),
-                                                                __float_as_uint(u[2 * m + 1]), false, false);
-                tr_s[m] = fmaxf(tr_s[m], (__uint_as_float(r[0]) + __uint_as_float(r[1])) * inv_sub);
+                for (int m = 0; m < 2; ++m) {
+                  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(u[2 * m]),
+                                                                  __float_as_uint(u[2 * m + 1]), false, false);
+                  tr_s[m] = fmaxf(tr_s[m], (__uint_as_float(r[0]) + __uint_as_float(r[1])) * inv_sub);
+                }
+              } else {
+#pragma unroll
+                for (int p = 0; p < 4; ++p) tr_s[p] = fmaxf(tr_s[p], u[p] * inv_sub);
               }
 #pragma unroll
               for (int e = 0; e < EPL; ++e) v[e] = 0.f;
@@ -470,13 +484,22 @@ __global__ __launch_bounds__(256) void summaries_kernel(const KVT* __restrict__ 
       }
     }
     if (TR && tr_on) {
-      // row group rg holds coordinates rg and 4 + rg of its lane's eight
       if (rg == 0) {
 #pragma unroll
         for (int e = 0; e < EPL; ++e) mu_s[cl * EPL + e][jj] = mean[e];
       }
-      sg_s[cl * EPL + rg][jj] = sqrtf(tr_s[0]);
-      sg_s[cl * EPL + 4 + rg][jj] = sqrtf(tr_s[1]);
+      const int row = lane >> 4;
+      if (LPR == 16 || (1 << sub_log2) >= R) {
+        // row r holds coordinates r and 4 + r of its lane's eight
+        sg_s[cl * EPL + row][jj] = sqrtf(tr_s[0]);
+        sg_s[cl * EPL + 4 + row][jj] = sqrtf(tr_s[1]);
+      } else {
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+          const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(tr_s[p]), __float_as_uint(tr_s[p]), false, false);
+          sg_s[cl * EPL + 2 * p + (row & 1)][jj] = sqrtf(fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1])));
+        }
+      }
     } else {
 #pragma unroll
       for (int e = 0; e < EPL; ++e) {
@@ -496,11 +519,11 @@ __global__ __launch_bounds__(256) void summaries_kernel(const KVT* __restrict__ 
   }
   __syncthreads();
   // whole rows of the dimension-major output (blocks j0 .. j0 + nv - 1)
-  const int nv = N - j0 < kSumBlocks ? (int)(N - j0) : kSumBlocks;
+  const int nv = N - j0 < NB ? (int)(N - j0) : NB;
   const int64_t ob = bg * D * g.ncap + j0;
   const bool f16 = g.stat_dtype == ETA_DT_F16, fp8 = g.stat_dtype == ETA_DT_FP8;
-  for (int idx = tid; idx < D * kSumBlocks; idx += 256) {
-    const int i = idx / kSumBlocks, jj = idx % kSumBlocks;
+  for (int idx = tid; idx < D * NB; idx += 256) {
+    const int i = idx / NB, jj = idx % NB;
     if (jj < nv) {
       const int64_t o = ob + (int64_t)i * g.ncap + jj;
       if (f16) {   // round to nearest even
@@ -2359,21 +2382,32 @@ hipError_t launch_summaries(const Geom& g, const void* k, const int32_t* seq_len
                             const eta_summary_t& s, hipStream_t stream, LaunchHook hook) {
   const int64_t nblk = prev_lens != nullptr ? max_new_blocks : g.cap / g.BS;
   if (nblk <= 0) return hipSuccess;
-  dim3 grid((unsigned)((nblk + kSumBlocks - 1) / kSumBlocks), g.Hkv, g.B);
+  // Blocks per workgroup: with 32 the records leave as whole 64- to 128-byte rows, but
+  // one block per wavefront (4) starts up to eight times the workgroups and makes them
+  // short.  32 wins where K alone fills the card several times over (512 MiB of K, 128-token
+  // blocks: 98 us against 105 with 4; 1 GiB, 64-token blocks: 203 against 216), 4 below
+  // (2 x 32K tokens, 2 kv heads, d = 128: 57 -> 11 us; 8 x 32000, 4 heads, d = 64,
+  // flat 31 -> 29, envelope of 4: 39 -> 32, and
+  // 62 before its sub-block sums took the transposed route); equal at 397 MB.
+  const int64_t kbytes = nblk * g.BS * g.Hkv * g.B * g.D * (g.kv_dtype == ETA_DT_F32 ? 4 : 2);
+  const bool nb32 = kbytes >= (int64_t(400) << 20);
+  const int nb = nb32 ? 32 : 4;
+  dim3 grid((unsigned)((nblk + nb - 1) / nb), g.Hkv, g.B);
   int sub_log2 = 0;
   while (sub_block > 0 && (1 << sub_log2) < sub_block) ++sub_log2;
   const int max_new = prev_lens != nullptr ? max_new_blocks : 0;
   return with_hook(hook, ETA_KERNEL_SUMMARIES, stream, [&] {
+#define ETA_SUM_E(D_, BS_, T_, ENV_, NB_)                                                       \
+  hipLaunchKernelGGL((summaries_kernel<D_, BS_, T_, ENV_, NB_>), grid, dim3(256), 0, stream,    \
+                     reinterpret_cast<const T_*>(k), g, seq_lens, prev_lens, max_new, sub_log2, \
+                     s.mu, s.sigma, s.max_norm);
 #define ETA_SUM(D_, BS_, T_)                                                                    \
   if (g.D == D_ && g.BS == BS_) {                                                               \
-    if (sub_block > 0)                                                                          \
-      hipLaunchKernelGGL((summaries_kernel<D_, BS_, T_, true>), grid, dim3(256), 0, stream,     \
-                         reinterpret_cast<const T_*>(k), g, seq_lens, prev_lens, max_new,       \
-                         sub_log2, s.mu, s.sigma, s.max_norm);                                  \
-    else                                                                                        \
-      hipLaunchKernelGGL((summaries_kernel<D_, BS_, T_, false>), grid, dim3(256), 0, stream,    \
-                         reinterpret_cast<const T_*>(k), g, seq_lens, prev_lens, max_new,       \
-                         sub_log2, s.mu, s.sigma, s.max_norm);                                  \
+    if (sub_block > 0) {                                                                        \
+      if (nb32) { ETA_SUM_E(D_, BS_, T_, true, 32) } else { ETA_SUM_E(D_, BS_, T_, true, 4) }   \
+    } else {                                                                                    \
+      if (nb32) { ETA_SUM_E(D_, BS_, T_, false, 32) } else { ETA_SUM_E(D_, BS_, T_, false, 4) } \
+    }                                                                                           \
   }
     if (g.kv_dtype == ETA_DT_F32) {
       ETA_SUM(64, 64, float) ETA_SUM(64, 128, float) ETA_SUM(128, 64, float) ETA_SUM(128, 128, float)
@@ -2382,6 +2416,7 @@ hipError_t launch_summaries(const Geom& g, const void* k, const int32_t* seq_len
       ETA_SUM(128, 128, uint16_t)
     }
 #undef ETA_SUM
+#undef ETA_SUM_E
   });
 }
 

@@ -174,3 +174,42 @@ def test_decode_on_envelope_summaries_matches_oracle(sub, lwb):
     stats = compare(wl, g, orc, tau_o, np_inputs=np_in, union_counts=g.union_counts)
     frac = float(g.mask.float().mean())
     say(f"[gpu] envelope sub {sub} lwb {lwb}: {stats}, mask density {frac:.3f}")
+
+
+@pytest.mark.parametrize("d,b,sub", [(64, 64, 1), (64, 64, 32), (64, 64, 64), (64, 128, 2), (64, 128, 8),
+                                     (64, 128, 128), (128, 64, 64), (128, 128, 2)])
+def test_envelope_sub_block_edges(d, b, sub):
+    """Sub-blocks below, at and above the row groups that one load covers."""
+    ENVELOPE_CASES.append((2, 1, d, b, [b * 9 + 5, b * 2], torch.bfloat16, (sub,)))
+    try:
+        test_envelope_matches_oracle(len(ENVELOPE_CASES) - 1)
+    finally:
+        ENVELOPE_CASES.pop()
+
+
+@pytest.mark.parametrize("d,b,sub,rec", [(128, 128, 0, torch.float32), (128, 64, 4, torch.float16),
+                                         (64, 64, 4, torch.float8_e4m3fn), (64, 64, 0, torch.float32),
+                                         (64, 128, 8, torch.float16)])
+def test_large_and_small_builds_write_the_same_records(d, b, sub, rec):
+    """A cache large enough for 32 blocks per workgroup and its first part alone, built with
+    4 per workgroup: the same bits, ragged ends included."""
+    T = 512 * 1024 * 1024 // (4 * d * 2) + 3 * b + 7          # 4 kv heads, over 512 MiB
+    cut = 45 * b + 3
+    gen = torch.Generator(device="cuda").manual_seed(d + b + sub)
+    k = torch.empty(1, 4, T, d, device="cuda", dtype=torch.bfloat16)
+    for h in range(4):
+        k[0, h] = torch.randn(T, d, generator=gen, device="cuda").to(torch.bfloat16)
+    kw = dict(sub_block=sub, stat_dtype=rec)
+    big = eta.build_block_summaries(k, torch.tensor([T], dtype=torch.int32, device="cuda"), b, **kw)
+    part = eta.build_block_summaries(k[:, :, :cut], torch.tensor([cut], dtype=torch.int32, device="cuda"),
+                                     b, **kw)
+    first = T // b - 11                          # the last blocks: a shorter workgroup
+    end = eta.build_block_summaries(k[:, :, first * b:],
+                                    torch.tensor([T - first * b], dtype=torch.int32, device="cuda"), b, **kw)
+    n = cut // b
+    bits = lambda t: t.contiguous().view(torch.uint8)
+    for name in ("mu", "sigma"):
+        assert torch.equal(bits(getattr(big, name)[..., :n]), bits(getattr(part, name)[..., :n]))
+    assert torch.equal(big.max_norm[..., :n], part.max_norm[..., :n])
+    for name in ("mu", "sigma", "max_norm"):
+        assert torch.equal(bits(getattr(big, name)[..., first:]), bits(getattr(end, name)[..., :11]))
