@@ -233,6 +233,32 @@ SplitPlan plan_splits(const Geom& g, int num_splits) {
   return SplitPlan{S, (int)(S * BG)};
 }
 
+// Several sequences: workgroups dealt to the (sequence, kv head) groups in
+// proportion to their lengths, at most one per 256 tokens of capacity, i.e. one tile per
+// wavefront (a uniform count left the short sequences' workgroups idle, and 2048 tokens or
+// more to each: 8 ragged sequences up to 32K, 16/4 heads, d = 128: 79 -> 67 us; 2 x 4000
+// tokens, 8/2 heads: 69 -> 17 with 256 tokens, 20 with 512, 31 with 1024; equal from 15K
+// tokens on).
+constexpr int kDenseTokens = 256;
+
+int dense_prop_workgroups(const Geom& g) {
+  const int64_t BG = (int64_t)g.B * g.Hkv;
+  int64_t W = 8 * BG;
+  W = W < kPropSplits ? kPropSplits : (W > kPropMaxSplits ? kPropMaxSplits : W);
+  const int64_t most = BG * (g.cap / kDenseTokens > 1 ? g.cap / kDenseTokens : 1);
+  if (W > most) W = most;
+  return (int)(W < BG ? BG : W);
+}
+
+int dense_splits(const Geom& g, int num_splits) {
+  if (num_splits > 0) return num_splits;
+  const int64_t BG = (int64_t)g.B * g.Hkv;
+  // (the kernel adds the groups' tiles in 32 bits)
+  if (g.B > 1 && BG <= kPropMaxGroups && BG * (g.cap / 64 + 1) < (int64_t(1) << 30))
+    return dense_prop_workgroups(g) > BG ? 0 : 1;
+  return default_splits(g);
+}
+
 size_t decode_ws_bytes(const Geom& g, const SplitPlan& sp, DecodeWs* c, void* base) {
   const size_t nb = (size_t)g.B * g.Hkv * g.ncap;
   const size_t BG = (size_t)g.B * g.Hkv, BH = (size_t)g.B * g.Hq;
@@ -273,16 +299,21 @@ size_t decode_ws_bytes(const Geom& g, const SplitPlan& sp, DecodeWs* c, void* ba
 }
 
 size_t dense_ws_bytes(const Geom& g, int S, DecodeWs* c, void* base) {
+  const size_t BG = (size_t)g.B * g.Hkv;
+  const size_t W = S > 0 ? BG * S : (size_t)dense_prop_workgroups(g);
   size_t off = 0;
   const size_t o_ml = off;
-  off = align256(off + (size_t)g.B * g.Hq * S * 8);
+  off = align256(off + W * g.G * 8);
   const size_t o_acc = off;
-  off = align256(off + (size_t)g.B * g.Hq * S * g.D * 4);
+  off = align256(off + W * g.G * g.D * 4);
+  const size_t o_pl = off;
+  if (S == 0) off = align256(off + BG * 8);
   if (c && base) {
     char* p = static_cast<char*>(base);
     *c = DecodeWs{};
     c->part_ml = reinterpret_cast<float2*>(p + o_ml);
     c->part_acc = reinterpret_cast<float*>(p + o_acc);
+    if (S == 0) c->plan = reinterpret_cast<int2*>(p + o_pl);
   }
   return off;
 }
@@ -567,7 +598,7 @@ eta_status_t eta_dense_workspace_size(const eta_kv_desc_t* kv, int32_t num_split
   if (num_splits < 0 || num_splits > kMaxSplits)
     return fail(ETA_ERR_INVALID_ARG, "num_splits must be in [0, %d]", kMaxSplits);
   if (!bytes) return fail(ETA_ERR_INVALID_ARG, "bytes is NULL");
-  const int S = num_splits > 0 ? num_splits : default_splits(g);
+  const int S = dense_splits(g, num_splits);
   *bytes = dense_ws_bytes(g, S, nullptr, nullptr);
   return ok();
 }
@@ -586,7 +617,7 @@ eta_status_t eta_dense_decode(const eta_kv_desc_t* kv, int32_t q_dtype, const vo
     return fail(ETA_ERR_INVALID_ARG, "q, k, v, seq_lens and out must be non-NULL");
   if (!aligned16(q) || !aligned16(k) || !aligned16(v) || !aligned16(seq_lens) || !aligned16(out))
     return fail(ETA_ERR_INVALID_ARG, "device pointers must be 16-byte aligned");
-  const int S = num_splits > 0 ? num_splits : default_splits(g);
+  const int S = dense_splits(g, num_splits);
   if (!workspace) return fail(ETA_ERR_WORKSPACE, "workspace is NULL");
   if (reinterpret_cast<uintptr_t>(workspace) & 255u)
     return fail(ETA_ERR_WORKSPACE, "workspace must be 256-byte aligned");

@@ -66,6 +66,10 @@ SplitPlan plan_splits(const Geom& g, int num_splits);
 size_t decode_ws_bytes(const Geom& g, const SplitPlan& sp, DecodeWs* carve, void* base);
 size_t dense_ws_bytes(const Geom& g, int S, DecodeWs* carve, void* base);
 int default_splits(const Geom& g);
+// Dense decode: splits per group for a call's num_splits, 0 for the proportional
+// plan, and that plan's workgroups.
+int dense_splits(const Geom& g, int num_splits);
+int dense_prop_workgroups(const Geom& g);
 
 struct DecodeCfg {
   float beta, z, offset_a;

@@ -1361,7 +1361,12 @@ struct Bf16Tile {
   template <typename TB, typename BITS>
   __device__ __forceinline__ void stream(int ntiles, TB tile_base, BITS tile_bits, SoftState<G, 2>& ss) const {
     if (ntiles <= 0) return;
-    constexpr int NR = NV / 4;                   // V loads per quarter of the tile
+    // parts of V: a part of the next tile is requested when this tile's is consumed.  One
+    // part for the dense baseline (32 x 64K ragged, d = 128: 865 us with four, 859 with two,
+    // 854 with one), two where the gate leaves longer gaps (32 ragged sequences, 10%:
+    // 353.5 us with four, 350.4 with two; 512K equal)
+    constexpr int NCK = DENSE ? 1 : 2;
+    constexpr int NR = NV / NCK;
     uint4 kr[DC];
     uint32_t vr[NV];
     auto load_k = [&](int64_t tb) {
@@ -1377,8 +1382,8 @@ struct Bf16Tile {
       for (int t = t0; t < t0 + NR; ++t) vr[t] = load_v_pair(vt + TPL * t * st);
     };
     // One tile: scores on the MFMAs, then (MORE) the next tile's K loads into the
-    // freed K registers, the softmax update, p.V in four quarters, each followed by
-    // (MORE) that quarter of the next tile's V loads.  The last tile is peeled
+    // freed K registers, the softmax update, p.V in NCK parts, each followed by
+    // (MORE) that part of the next tile's V loads.  The last tile is peeled
     // (MORE = false) so that the loads inside the loop are unconditional: a
     // conditional reload would keep two copies of the K/V registers alive across
     // the branch.
@@ -1395,7 +1400,7 @@ struct Bf16Tile {
       }
       weights(c, true, bits, (tb + lane) == self_t, ss);
 #pragma unroll
-      for (int qt = 0; qt < 4; ++qt) {
+      for (int qt = 0; qt < NCK; ++qt) {
 #pragma unroll
         for (int t = NR * qt; t < NR * (qt + 1); ++t) pv(t, vr[t], ss);
         if constexpr (MORE) {
@@ -1409,7 +1414,7 @@ struct Bf16Tile {
     int64_t tb = tile_base(0);
     load_k(tb);
 #pragma unroll
-    for (int qt = 0; qt < 4; ++qt) load_v_rows(tb, NR * qt);
+    for (int qt = 0; qt < NCK; ++qt) load_v_rows(tb, NR * qt);
     for (int u = 0; u + 1 < ntiles; ++u) {
       const int64_t tbn = tile_base(u + 1);
       tile(u, tb, tbn, std::integral_constant<bool, true>{});
@@ -1446,7 +1451,7 @@ __global__ __launch_bounds__(64 * kSplitWaves) void split_kernel(SplitArgs a) {
   __shared__ uint8_t item_bits[kItemChunk];
   __shared__ uint8_t item_sub[kItemChunk];
   __shared__ int own_s[3];                               // proportional: (group, first split, splits)
-  __shared__ int wsum2_s[DENSE ? 1 : kPropMaxGroups / NT][NW];  // proportional: split scan's wavefront sums
+  __shared__ int wsum2_s[PROP ? kPropMaxGroups / NT : 1][NW];  // proportional: split scan's wavefront sums
   __shared__ int cnt_s[DENSE ? 1 : kPropMaxCounts + 1];  // proportional: prefix of every tile count
   __shared__ int wtail_s[NW];
   __shared__ float rbest_s[DENSE ? 1 : G][kRescueTiles];
@@ -1459,12 +1464,11 @@ __global__ __launch_bounds__(64 * kSplitWaves) void split_kernel(SplitArgs a) {
   // ---- which (sequence, kv head) and split.  Uniform plan (PROP false): S splits
   // per group, grid (S, Hkv, B).  Proportional plan (PROP, several sequences): a
   // 1-D grid whose workgroups are dealt to the groups in proportion to their
-  // union's 64-token tiles (at least one each), so short and long unions finish
+  // union's 64-token tiles (dense: their sequence's; at least one each), so short and long unions finish
   // together in one round.  The two plans are separate instantiations, so neither
   // carries the other's code.
   constexpr int SPB = BF ? BS / 64 : 1;
   constexpr bool uniform = !PROP;
-  static_assert(!(DENSE && PROP), "the dense baseline takes the uniform plan");
   int b, gh, s, S, first;
   const int32_t* tc = nullptr;     // uniform: the group's tile counts
   const int* pref = pref_s;        // exclusive prefix of the group's tile counts ...
@@ -1487,11 +1491,12 @@ __global__ __launch_bounds__(64 * kSplitWaves) void split_kernel(SplitArgs a) {
     static_assert(CPT * NT == kPropMaxCounts && GPT * NT == kPropMaxGroups, "whole shares");
     // (unconditional loads from clamped indexes, masked afterwards: a load under a
     // branch is waited for inside the branch, one round trip each)
+    // (dense: no counts; every block of a sequence is work)
     int cv[CPT], tails[GPT];
 #pragma unroll
     for (int k = 0; k < CPT; ++k) {
       const int i = tid * CPT + k;
-      cv[k] = a.tile_cnt[i < nc ? i : 0];
+      cv[k] = DENSE ? 0 : a.tile_cnt[i < nc ? i : 0];
     }
     {
       // group x = r NT + tid is (sequence x / Hkv, kv head x % Hkv)
@@ -1514,7 +1519,7 @@ __global__ __launch_bounds__(64 * kSplitWaves) void split_kernel(SplitArgs a) {
       const int x = r * NT + tid;
       const int64_t len = tails[r] < 0 ? 0 : (tails[r] > g.cap ? g.cap : tails[r]);
       // a group's work is its union's tiles plus one for a partial tail
-      tails[r] = x < BG ? group_work(0, SPB, len, BS) : 0;
+      tails[r] = x < BG ? group_work(DENSE ? (int)(len / BS) : 0, SPB, len, BS) : 0;
       ntl += tails[r];
     }
     int run = 0;
@@ -1538,19 +1543,21 @@ __global__ __launch_bounds__(64 * kSplitWaves) void split_kernel(SplitArgs a) {
       ntails += wtail_s[k];
     }
     const int ex = woff + incl - run;
+    if constexpr (!DENSE) {
 #pragma unroll
-    for (int k = 0; k < CPT; ++k) cnt_s[tid * CPT + k] = ex + cv[k];
-    if (tid == NT - 1) cnt_s[kPropMaxCounts] = ex + run;
-    __syncthreads();
+      for (int k = 0; k < CPT; ++k) cnt_s[tid * CPT + k] = ex + cv[k];
+      if (tid == NT - 1) cnt_s[kPropMaxCounts] = ex + run;
+      __syncthreads();
+    }
     // splits per group (integer work: the total does not depend on the order)
     const int64_t UT = (int64_t)tot * SPB + ntails;
     int nsp[GPT], inc[GPT];
 #pragma unroll
     for (int r = 0; r < GPT; ++r) {
       const int x = r * NT + tid;
-      nsp[r] = x < BG ? group_splits((cnt_s[(x + 1) * nct] - cnt_s[x * nct]) * SPB + tails[r],
-                                     UT, W, BG)
-                      : 0;
+      int work = tails[r];
+      if constexpr (!DENSE) work += x < BG ? (cnt_s[(x + 1) * nct] - cnt_s[x * nct]) * SPB : 0;
+      nsp[r] = x < BG ? group_splits(work, UT, W, BG) : 0;
     }
     // one scan per round of NT groups in use
 #pragma unroll
@@ -1590,8 +1597,12 @@ __global__ __launch_bounds__(64 * kSplitWaves) void split_kernel(SplitArgs a) {
     first = own_s[1];
     s = me - first;
     S = own_s[2];
-    pref = cnt_s + bgi * nct;
-    pbase = pref[0];
+    if constexpr (DENSE) {
+      if (s == 0 && tid == 0) a.plan[bgi] = make_int2(first, S);
+    } else {
+      pref = cnt_s + bgi * nct;
+      pbase = pref[0];
+    }
   }
   const int64_t hq0 = (int64_t)b * g.Hq + (int64_t)gh * G;
   const int64_t bg = (int64_t)b * g.Hkv + gh;
@@ -2354,11 +2365,11 @@ void launch_split_kv(const Geom& g, const SplitPlan& pl, const SplitArgs& sp, hi
   const dim3 grid = pl.S > 0 ? dim3(pl.S, g.Hkv, g.B) : dim3(pl.W);
 #define ETA_SPL(D_, BS_, G_)                                                                    \
   if (g.D == D_ && g.BS == BS_ && g.G == G_) {                                                  \
-    if (DENSE || pl.S > 0)                                                                      \
+    if (pl.S > 0)                                                                               \
       hipLaunchKernelGGL((split_kernel<D_, BS_, G_, KVT, DENSE, false>), grid, dim3(64 * kSplitWaves), 0, \
                          stream, sp);                                                           \
     else                                                                                        \
-      hipLaunchKernelGGL((split_kernel<D_, BS_, G_, KVT, DENSE, !DENSE>), grid, dim3(64 * kSplitWaves), 0, \
+      hipLaunchKernelGGL((split_kernel<D_, BS_, G_, KVT, DENSE, true>), grid, dim3(64 * kSplitWaves), 0, \
                          stream, sp);                                                           \
   }
 #define ETA_SPL_G(D_, BS_) ETA_SPL(D_, BS_, 1) ETA_SPL(D_, BS_, 2) ETA_SPL(D_, BS_, 4) ETA_SPL(D_, BS_, 8)
@@ -2551,17 +2562,20 @@ hipError_t launch_calib_solve(const eta_calib_desc_t& cd, const eta_calib_state_
   });
 }
 
+// S == 0: the proportional plan (work known from the lengths alone), see
+// dense_prop_workgroups.
 hipError_t launch_dense(const Geom& g, int S, int q_dtype, const void* q, const void* k,
                         const void* v, const int32_t* seq_lens, void* out, const DecodeWs& ws,
                         hipStream_t stream, LaunchHook hook) {
+  const SplitPlan plan{S, S > 0 ? S * g.B * g.Hkv : dense_prop_workgroups(g)};
   SplitArgs sp{q, k, v, seq_lens, nullptr, nullptr, nullptr, ws.part_ml, ws.part_acc,
-               nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, out,
+               nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, ws.plan, nullptr, out,
                nullptr, nullptr, g, q_dtype, 0.f, 0.f, 0, 0};
   hipError_t e = with_hook(hook, ETA_KERNEL_DENSE_SPLIT, stream,
-                           [&] { launch_split_impl<true>(g, SplitPlan{S, S * g.B * g.Hkv}, sp, stream); });
+                           [&] { launch_split_impl<true>(g, plan, sp, stream); });
   if (e != hipSuccess || S == 1) return e;     // one split per group wrote the output
-  CombineArgs ca{ws.part_ml, ws.part_acc, nullptr, nullptr, seq_lens, nullptr, nullptr, nullptr,
-                 nullptr, nullptr, out, g, q_dtype, S};
+  CombineArgs ca{ws.part_ml, ws.part_acc, nullptr, nullptr, seq_lens, nullptr, nullptr,
+                 S > 0 ? nullptr : ws.plan, nullptr, nullptr, out, g, q_dtype, S};
   return with_hook(hook, ETA_KERNEL_DENSE_COMBINE, stream,
                    [&] { launch_combine_impl(g, ca, stream); });
 }

@@ -13,7 +13,7 @@ import pytest
 import torch
 
 import oracle
-from gpu_support import (GpuRun, calibrate_bias, compare, f16_band, f16_record_ranges,
+from gpu_support import (TOL, GpuRun, calibrate_bias, compare, f16_band, f16_record_ranges,
                          oracle_inputs, oracle_summaries, require_gpu, run_gpu, run_oracle, say)
 from paper_2609_20888_amd import eta
 from synth import as_numpy, config1, config2, config3, config4, config5, make_workload, place_bias
@@ -305,6 +305,44 @@ def test_dense_decode_matches_oracle():
                 for h in range(8):
                     ref = r.o[bb, h]
                     assert np.max(np.abs(o[bb, h] - ref)) / np.max(np.abs(ref)) <= tol, (splits, bb, h)
+
+
+DENSE_PLAN = {
+    # name: (B, Hq, Hkv, d, block, T_cap, lens, dtype)
+    "ragged_empty_and_short": (5, 8, 2, 128, 64, 3000, [3000, 0, 1, 63, 1500], torch.bfloat16),
+    "fp32_blocks_of_128": (3, 4, 4, 64, 128, 2100, [2100, 127, 129], torch.float32),
+    "gqa8_d64": (2, 16, 2, 64, 64, 1999, [700, 1999], torch.bfloat16),
+    "all_empty": (2, 2, 1, 128, 64, 1024, [0, 0], torch.bfloat16),
+    "odd_heads_300_groups": (100, 3, 3, 64, 64, 600, [(37 * i) % 601 for i in range(100)], torch.bfloat16),
+    "past_the_group_table": (520, 2, 2, 64, 64, 300, [(53 * i) % 301 for i in range(520)], torch.bfloat16),
+    "one_split_per_group": (4, 4, 1, 128, 64, 500, [500, 256, 255, 3], torch.bfloat16),
+}
+
+
+@pytest.mark.parametrize("name", sorted(DENSE_PLAN))
+def test_dense_decode_plan_shapes(name):
+    """The dense decode's split plans for several sequences (dealt by length; one split per
+    group on a short capacity; uniform past the plan's table), every row."""
+    B, Hq, Hkv, d, b, cap, lens, dt = DENSE_PLAN[name]
+    wl = make_workload(B=B, Hq=Hq, Hkv=Hkv, d=d, block=b, seq_lens=lens, T_cap=cap, dtype=dt,
+                       predictor=False, tau_const=0.0, seed=B + d)
+    dev = torch.device("cuda")
+    sl = torch.tensor(lens, dtype=torch.int32, device=dev)
+    args = (wl.q.to(dev), wl.k.to(dev), wl.v.to(dev), sl)
+    out = eta.dense_decode(*args, block_size=b)
+    again = eta.dense_decode(*args, block_size=b)
+    torch.cuda.synchronize()
+    assert torch.equal(out, again)
+    q, k, v = oracle_inputs(wl)
+    r = oracle.decode(q, k, v, lens, np.zeros((B, Hq)), block_size=b, screen_all=True, gate_off=True)
+    o, tol = out.float().cpu().numpy(), TOL[dt]
+    for bb in range(B):
+        if lens[bb] == 0:
+            assert np.all(o[bb] == 0)
+            continue
+        for h in range(Hq):
+            ref = r.o[bb, h]
+            assert np.max(np.abs(o[bb, h] - ref)) <= tol * np.max(np.abs(ref)), (bb, h)
 
 
 # ------------------------------------------------------------------ full-size workloads
