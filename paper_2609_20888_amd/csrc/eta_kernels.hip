@@ -1225,7 +1225,7 @@ __device__ __forceinline__ void attend_f32(const float* __restrict__ kb, const f
     float sc[G], p[G];
 #pragma unroll
     for (int h = 0; h < G; ++h)
-      sc[h] = gated<DENSE>(dot[h], valid && ((bits >> h) & 1u), ung, kLog2e, nbs, bt_s[h]);
+      sc[h] = gated<DENSE>(dot[h], valid && ((bits >> h) & 1u), ung, 1.0f, nbs, bt_s[h]);
     ss.step(sc, p);
 #pragma unroll
     for (int h = 0; h < G; ++h) p_s[lane][h] = p[h];
@@ -1438,7 +1438,7 @@ __global__ __launch_bounds__(64 * kSplitWaves) void split_kernel(SplitArgs a) {
   constexpr int DC = D / 8;
   const Geom& g = a.g;
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
-  __shared__ float qf_s[BF ? 1 : D][G];                  // fp32 path: scaled q
+  __shared__ float qf_s[BF ? 1 : D][G];                  // fp32 path: q log2 e / sqrt(d)
   __shared__ bf16x8 qa_s[BF ? NQ * 2 * 4 * DC : 1];      // bf16 path: q chunks (hi, lo)
   __shared__ bf16x8 qz_s[BF ? (2 * NQ - 1) * 4 * DC + DC : 1];  // zeros, read off A's diagonal
   __shared__ float bt_s[G];
@@ -1667,7 +1667,7 @@ __global__ __launch_bounds__(64 * kSplitWaves) void split_kernel(SplitArgs a) {
         qa16[(((quad * 2 + 0) * 4 + rr) * DC) * 8 + i] = hi;
         qa16[(((quad * 2 + 1) * 4 + rr) * DC) * 8 + i] = lo;
       } else {
-        qf_s[i][hh] = x * scale;
+        qf_s[i][hh] = x * (scale * kLog2e);
       }
     }
   }
@@ -1789,7 +1789,7 @@ __global__ __launch_bounds__(64 * kSplitWaves) void split_kernel(SplitArgs a) {
       bt.attend(t0, nvalid, bits, ss);
     else
       attend_f32<D, G, DENSE>(kb, vb, g.st, t0, nvalid, bits, qf_s, bt_s,
-                              reinterpret_cast<float (*)[G]>(p_s[w]), -a.beta * kLog2e, self_t, lane, ss);
+                              reinterpret_cast<float (*)[G]>(p_s[w]), -a.beta, self_t, lane, ss);
   };
   constexpr uint32_t all_bits = (1u << G) - 1u;
   // The split's items are resolved (union slot -> block id -> head bits) in
