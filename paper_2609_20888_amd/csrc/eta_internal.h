@@ -46,7 +46,7 @@ struct DecodeWs {
                              //                  t * kScreenTile)
   int32_t* tile_cnt;         // [B][Hkv][n_tiles] union blocks per tile
   int32_t* head_cnt;         // [B][Hq][n_tiles]  selected blocks per head per tile
-  float2* part_ml;           // [W][G]            (running max, running sum) per split and head
+  float2* part_ml;           // [W][G]            (reference max in base-2 units, sum) per split and head
   float* part_acc;           // [W][G][D]         unnormalised output per split and head
   float* tau;                // [B][Hq]           thresholds predicted by the screening kernel
 };

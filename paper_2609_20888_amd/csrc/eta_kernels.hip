@@ -2235,7 +2235,7 @@ struct CombineArgs {
 // owns head dimension i and the splits s = part, part + P, ... (P = 512 / D):
 // it issues the loads of its splits' maxima and accumulators together, the
 // workgroup takes the largest maximum, and each thread adds its weighted
-// accumulators exp(m_s - m) acc_s[i] (the part-0 threads also the weighted
+// accumulators 2^(m_s - m) acc_s[i] (the part-0 threads also the weighted
 // sums l_s); the P partial sums are then added in order.  (512 threads: 0.5 us
 // faster than 1024 at 64 splits, fewer wavefronts in each reduction; 256 left
 // 32 splits per thread and was no faster.)
