@@ -312,7 +312,9 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(PrefillArgs a) {
     if (u == 0 || __ballot(mx > 8.0f) != 0ull) {
       const float rm = row2_max(mx);
       const float dm = rm == kNegInf ? 0.f : (u == 0 ? rm : fmaxf(rm, 0.f));
-      const float alpha = __builtin_amdgcn_exp2f(-dm);
+      // (the first unit's move scales nothing: the sums are zero, and 2^-dm overflows
+      // where the row's scores are below -128)
+      const float alpha = u == 0 ? 1.0f : __builtin_amdgcn_exp2f(-dm);
       m_i += dm;
       l_i *= alpha;
 #pragma unroll

@@ -7,6 +7,8 @@ gate row sums R to 1e-4 relative (fp32 sums of gates whose scores differ from
 fp64 by fp32 accumulation); log-sum-exp L to 1e-4 absolute.  Rows past a
 sequence's length are zero / 0 / -inf.
 """
+import math
+
 import numpy as np
 import pytest
 import torch
@@ -107,6 +109,58 @@ def test_prefill_unit_edges(d, Hq, Hkv, T, lens):
                 assert np.max(np.abs(o[b, h, :n] - ref)) <= 2e-2 * np.max(np.abs(ref)), (add, b, h)
             np.testing.assert_allclose(Rg[b, :, :n], r.r[b, :, :n], rtol=1e-4, atol=1e-5)
             np.testing.assert_allclose(Lg[b, :, :n], r.lse[b, :, :n], rtol=0, atol=1e-4)
+
+
+def _prefill_vs_oracle(q, k, v, tau, lens, **kw):
+    """Launch and compare every row (module docstring's tolerances); returns (out, R, L)."""
+    dev = torch.device("cuda")
+    sl = torch.tensor(lens, dtype=torch.int32, device=dev)
+    out, R, L = eta.gated_prefill(q.to(dev), k.to(dev), v.to(dev), tau.to(dev), sl, beta=4.0, **kw)
+    torch.cuda.synchronize()
+    return out.float().cpu().numpy(), R.cpu().numpy(), L.cpu().numpy()
+
+
+def _check_all(got, r, lens, tag="", lse_atol=1e-4):
+    o, Rg, Lg = got
+    for b, n in enumerate(lens):
+        assert np.all(o[b, :, n:] == 0) and np.all(Rg[b, :, n:] == 0)
+        assert np.all(np.isneginf(Lg[b, :, n:]))
+        for h in range(o.shape[1] if n else 0):
+            ref = r.o[b, h, :n]
+            err = np.max(np.abs(o[b, h, :n] - ref), axis=1) / np.max(np.abs(ref), axis=1)
+            assert np.max(err) <= 2e-2, (tag, b, h, int(np.argmax(err)), float(np.max(err)))
+        np.testing.assert_allclose(Rg[b, :, :n], r.r[b, :, :n], rtol=1e-4, atol=1e-5)
+        np.testing.assert_allclose(Lg[b, :, :n], r.lse[b, :, :n], rtol=0, atol=lse_atol)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("T", [1, 33, 64, 97, 200])
+@pytest.mark.parametrize("mode", ["open_32", "open_64", "open_all", "closed_additive"])
+def test_prefill_rows_whose_first_keys_score_very_low(mode, T, d):
+    """The first 32, 64 or all keys score about -103 (2^-149 below weight one: past where
+    an fp32 exponential of the reference's move overflows) with the gates open, or every
+    key but the row's own is shut 100 below by the additive gate.  The reference of the
+    first unit must not be scaled into the empty accumulators.  (Scores near 110: d fp32
+    additions add up to d 2^-24 110 to the log-sum-exp's tolerance.)"""
+    gen = torch.Generator().manual_seed(T + d)
+    q = 0.3 * torch.randn(1, 2, T, d, generator=gen)
+    k = 0.3 * torch.randn(1, 1, T, d, generator=gen)
+    v = torch.randn(1, 1, T, d, generator=gen).to(torch.bfloat16)
+    kw = {}
+    if mode == "closed_additive":
+        tau = torch.full((1, 2, T), float("inf"))
+        kw = dict(additive=True, C=100.0)
+    else:
+        tau = torch.full((1, 2, T), float("-inf"))
+        low = {"open_32": 32, "open_64": 64, "open_all": T}[mode]
+        q[..., 0] = 8.0
+        k[..., 0] = -2.0 * math.sqrt(d) / 8.0
+        k[:, :, :low, 0] = -103.0 * math.sqrt(d) / 8.0
+    q, k = q.to(torch.bfloat16), k.to(torch.bfloat16)
+    got = _prefill_vs_oracle(q, k, v, tau, [T], **kw)
+    r = oracle.prefill(as_numpy(q), as_numpy(k), as_numpy(v), tau.numpy().astype(np.float64), [T],
+                       beta=4.0, **kw)
+    _check_all(got, r, [T], mode, lse_atol=1e-4 + d * 2.0 ** -24 * 110)
 
 
 def _check_rows(o, R, L, r, rows, lens):
