@@ -163,6 +163,35 @@ def test_prefill_rows_whose_first_keys_score_very_low(mode, T, d):
     _check_all(got, r, [T], mode, lse_atol=1e-4 + d * 2.0 ** -24 * 110)
 
 
+@pytest.mark.parametrize("d", [64, 128])
+def test_prefill_largest_weight_of_the_first_64_keys_is_exact(d):
+    """Key 40 outweighs all others (by 2^4 .. 2^7.5, another fraction in every row) and only
+    its value is not zero, so an output row is v times one weight over the sum.  The
+    reference maximum covers the first 64 keys, so that weight is exactly one in bf16 and
+    the row's mean relative error is that of the output's own rounding: each value's is
+    uniform within 2^-8 (values in [1, 2)), a row's mean of d of them has a standard
+    deviation below 2^-8 / sqrt(3 d) <= 2.9e-4.  Rounding the weight would add up to 2^-8
+    (rms 1.6e-3) to every value of a row alike."""
+    T = 64
+    q, k = torch.zeros(1, 2, T, d), torch.zeros(1, 1, T, d)
+    # scores S = q0 k0 / sqrt(d), 4 .. 7.5 in base-2 units, steps that bf16 q0 resolves
+    k[..., 40, 0] = 1.0
+    x = torch.linspace(4.0, 7.5, 2 * T).view(1, 2, T) * math.log(2.0) * math.sqrt(d)
+    q[..., 0] = x
+    v = torch.zeros(1, 1, T, d)
+    gen = torch.Generator().manual_seed(d)
+    v[..., 40, :] = (1.0 + torch.rand(d, generator=gen)) * (1 - 2 * torch.randint(0, 2, (d,), generator=gen))
+    q, k, v = (t.to(torch.bfloat16) for t in (q, k, v))
+    tau = torch.full((1, 2, T), float("-inf"))
+    o, _, _ = _prefill_vs_oracle(q, k, v, tau, [T])
+    r = oracle.prefill(as_numpy(q), as_numpy(k), as_numpy(v), tau.numpy().astype(np.float64), [T],
+                       beta=4.0)
+    mean = (o[0, :, 40:] / r.o[0, :, 40:] - 1.0).mean(axis=-1)
+    rms = float(np.sqrt(np.mean(mean ** 2)))
+    say(f"[gpu] prefill d={d}: rms over rows of the mean relative error {rms:.2e}")
+    assert rms <= 5e-4
+
+
 def _check_rows(o, R, L, r, rows, lens):
     worst = 0.0
     for n, (b, h, i) in enumerate(rows):
