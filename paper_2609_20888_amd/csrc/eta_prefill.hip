@@ -174,18 +174,19 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(PrefillArgs a) {
   auto dma = [&](const uint16_t* src, uint16_t (*tile)[kPfK * D], int kb) {
     const char* base = reinterpret_cast<const char*>(src + (int64_t)kb * kPfK * D);
     uint16_t* dst = tile[kb & 1] + 8 * 64 * w;
-    if ((kb + 1) * kPfK <= a.T) {
+    if ((kb + 1) * kPfK <= Tb) {
 #pragma unroll
       for (int j = 0; j < NI; ++j)
         __builtin_amdgcn_global_load_lds((const void*)(base + goff + 4096 * j),
                                          (__attribute__((address_space(3))) void*)(dst + 8 * 256 * j),
                                          16, 0, 0);
-    } else {                                         // rows past the cache read its last row
+    } else {          // rows past the sequence read its last row: whatever the cache holds
+                      // there, NaN too, would reach p.V (with weight 0)
 #pragma unroll
       for (int j = 0; j < NI; ++j) {
         const int row = RPJ * j + grow0;
         const uint32_t off = goff + 4096u * j -
-                             (uint32_t)(row - (min(kb * kPfK + row, a.T - 1) - kb * kPfK)) * (2u * D);
+                             (uint32_t)(row - (min(kb * kPfK + row, Tb - 1) - kb * kPfK)) * (2u * D);
         __builtin_amdgcn_global_load_lds((const void*)(base + off),
                                          (__attribute__((address_space(3))) void*)(dst + 8 * 256 * j),
                                          16, 0, 0);

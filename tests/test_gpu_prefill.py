@@ -192,6 +192,23 @@ def test_prefill_largest_weight_of_the_first_64_keys_is_exact(d):
     assert rms <= 5e-4
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("T,lens", [(130, [33, 65, 0]), (200, [97, 1, 200]), (64, [63, 32, 64]),
+                                    (256, [129, 191, 128])])
+def test_prefill_ignores_what_lies_past_the_sequence(d, T, lens):
+    """A cache's rows past a sequence's end hold anything: NaN in q, k and tau and NaN or
+    infinities in v there change nothing."""
+    q, k, v, tau = _inputs(3, 4, 2, T, d, seed=T + d)
+    clean = [as_numpy(q), as_numpy(k), as_numpy(v), tau.numpy().astype(np.float64)]
+    for b, n in enumerate(lens):
+        for t in (q, k, v, tau):
+            t[b, :, n:] = float("nan")
+        v[b, :, n::3] = float("inf")
+    got = _prefill_vs_oracle(q, k, v, tau, lens)
+    r = oracle.prefill(*clean, lens, beta=4.0)
+    _check_all(got, r, lens)
+
+
 def _check_rows(o, R, L, r, rows, lens):
     worst = 0.0
     for n, (b, h, i) in enumerate(rows):
