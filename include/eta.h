@@ -325,7 +325,10 @@ eta_status_t eta_decode_predicted_noalloc(const eta_kv_desc_t* kv, int32_t q_dty
  *   density[h]       += sigmoid(beta (S - tau[x][h][t])) / (t + 1)
  * in fixed point (units of 2^-40, integer adds, so the sums do not depend on
  * the order of the adds); eta_calib_solve then finds, per head, the c with
- *   sum_b H_b sigmoid(beta (s_b - c)) = density / total      (bisection, fp64)
+ *   sum_b H_b sigmoid(beta (s_b - c)) = density / total
+ * by bracketed Newton steps in fp64, to 1e-9 / beta (where the left side is flat, by
+ * bisection: the flat stretch's lower end, and for a saturated head, whose density is 0
+ * or the whole weight, an end of [lo - 60 / beta, hi + 60 / beta]);
  * H the normalised histogram, s_b = lo + (b + 1/2) w, total the sum of the
  * weights (sequences x T).  Scores are computed on the matrix cores from bf16
  * q and K with fp32 accumulation.

@@ -14,7 +14,7 @@
 //                                                           (Eq. mult_attn; App. "Chunked
 //                                                            Decoding and Two-Stage Reduction")
 //   combine_kernel    log-sum-exp merge of the partials      (same appendix)
-//   calib_kernel,     offline calibration histogram and bisection
+//   calib_kernel,     offline calibration histogram, and the root of its density
 //   calib_solve_kernel                                       (Alg. "calibration")
 // The gated prefill forward is in eta_prefill.hip.  The dense baseline reuses split_kernel / combine_kernel with every block and
 // no gate.
@@ -2122,9 +2122,15 @@ struct CalibSolveArgs {
 // then safeguarded Newton in fp64: a bracket [lo, hi] is kept as in bisection, the
 // next point is the Newton step where it lies inside the bracket, else the
 // midpoint.  Newton converges quadratically: after a step below 1e-9 / beta the
-// remaining error is below 1e-17 / beta.  One workgroup per head, sums in a fixed
-// order, all latency: bisection to adjacent fp64 values took 60 evaluations of
-// sixteen bins a thread, 142 us for 1024 bins; this takes 16 us.
+// remaining error is below 1e-17 / beta.  Where the slope is below 1e-6 beta a Newton
+// step says little (g's own roundings, about 1e-16, move it by more than 1e-10 / beta,
+// and where g equals the target over a stretch it is 0 at any point of it): there the
+// next point is the midpoint, down to a bracket of 1e-9 / beta, so a flat stretch ends
+// where bisection ends and a saturated head at the bracket's end.
+// One workgroup per head, sums in a fixed order, all latency: bisection to adjacent
+// fp64 values took 60 evaluations of sixteen bins a thread, 142 us for 1024 bins
+// (128 to 138 us for a saturated head); this takes 14.6 us (54 to 74; 4096 bins: 150
+// to 30, saturated 130 and 158 to 93 and 124).
 __global__ __launch_bounds__(kSolveThreads) void calib_solve_kernel(CalibSolveArgs a) {
   constexpr int PER = kCalibMaxBins / kSolveThreads;
   __shared__ double red[2][kSolveWaves][2];
@@ -2199,10 +2205,11 @@ __global__ __launch_bounds__(kSolveThreads) void calib_solve_kernel(CalibSolveAr
       dg *= a.beta / tot;                         // -dg/dc
       if (g > target) lo = m; else hi = m;
       const double mid = 0.5 * (lo + hi);
-      if (mid <= lo || mid >= hi) { m = mid; break; }
+      if ((hi - lo) * a.beta < 1e-9 || mid <= lo || mid >= hi) { m = mid; break; }
       const double step = (g - target) / dg, nx = m + step;
-      if (fabs(step) * a.beta < 1e-9) { m = nx; break; }
-      m = nx > lo && nx < hi ? nx : mid;          // (false for an infinite or NaN step)
+      const bool newton = dg > 1e-6 * a.beta;     // (false for NaN)
+      if (newton && fabs(step) * a.beta < 1e-9) { m = nx; break; }
+      m = newton && nx > lo && nx < hi ? nx : mid;
     }
   }
   if (tid == 0) {

@@ -138,6 +138,13 @@ def test_calibration_adds_up_over_calls_with_several_workgroups_per_head():
             assert np.array_equal(x, y)
 
 
+def _slope(hist, lo, hi, beta, c):
+    """-g'(c) / beta in [0, 1/4]."""
+    s = lo + (np.arange(hist.size) + 0.5) * (hi - lo) / hist.size
+    e = np.exp(-np.abs(beta * (s - c)))
+    return float(np.sum(hist * (e / (1 + e) ** 2)) / np.sum(hist))
+
+
 @pytest.mark.parametrize("tau", [-60.0, 60.0, 1e30])
 def test_saturated_gates_solve_to_the_end_of_the_bracket(tau):
     """Every gate fully open or shut (1e30: the gate's exponential overflows): the
@@ -149,6 +156,64 @@ def test_saturated_gates_solve_to_the_end_of_the_bracket(tau):
     for h in range(2):
         assert abs(target[h] - (1.0 if tau < 0 else 0.0)) <= 1e-7
         ref = oracle.calib_solve(hist[h] / eta.CALIB_UNIT, lo, hi, 4.0, float(target[h]))
-        g = [oracle.calib_g(hist[h] / eta.CALIB_UNIT, lo, hi, 4.0, float(v)) for v in (c[h], ref)]
-        # (where g is flat at fp64 precision, any point of the flat stretch solves it)
-        assert abs(g[0] - target[h]) <= abs(g[1] - target[h]) + 1e-12
+        # the solver's last interval, one rounding to fp32, and what 32 fp64 roundings of g
+        # move a root this far out by
+        sl = _slope(hist[h] / eta.CALIB_UNIT, lo, hi, 4.0, ref)
+        tol = 1e-9 / 4.0 + abs(ref) * U
+        if 0 < target[h] < 1:
+            tol += 32 * 2.0 ** -53 / sl / 4.0
+        assert abs(c[h] - ref) <= tol, (h, c[h], ref)
+
+
+def _solve_counts(hist, dens, *, beta, lo, hi):
+    """eta_calib_solve of given integer accumulators: hist [H][nb], dens [H]."""
+    H, nb = hist.shape
+    cal = eta.Calibrator(H, H, 64, beta=beta, lo=lo, hi=hi, num_bins=nb, device="cuda")
+    cal.hist.copy_(torch.from_numpy(hist.astype(np.int64)))
+    cal.density.copy_(torch.from_numpy(dens.astype(np.int64)))
+    c, target = cal.solve()
+    torch.cuda.synchronize()
+    return c.cpu().numpy().astype(np.float64), target.cpu().numpy()
+
+
+@pytest.mark.parametrize("nb", [1, 2, 777, 1025, 4096])
+@pytest.mark.parametrize("beta", [0.0625, 4.0, 300.0])     # (exact in fp32, as the descriptor holds it)
+def test_solve_returns_the_root(nb, beta):
+    """The constant is the root of g(c) = target that bisection of the same histogram and
+    density finds: within 1e-9 / beta (the solver's last step), what 32 fp64 roundings of
+    g move the root by, and one rounding to fp32."""
+    rng = np.random.default_rng(nb)
+    lo, hi, H = -8.0, 24.0, 8
+    hist = (rng.random((H, nb)) ** 4 * 2.0 ** 40).astype(np.int64) + 1
+    hist[1::2, nb // 3: 2 * nb // 3] = 0                 # a gap in every other head
+    frac = np.array([1e-4, 0.01, 0.1, 0.3, 0.6, 0.9, 0.99, 0.9999])
+    dens = np.rint(hist.sum(axis=1) * frac).astype(np.int64)
+    c, target = _solve_counts(hist, dens, beta=beta, lo=lo, hi=hi)
+    for h in range(H):
+        H64 = hist[h].astype(np.float64)
+        ref = oracle.calib_solve(H64, lo, hi, beta, float(target[h]))
+        sl = _slope(H64, lo, hi, beta, ref)
+        tol = (1e-9 + 32 * 2.0 ** -53 / max(sl, 1e-300)) / beta + abs(ref) * U
+        assert abs(c[h] - ref) <= tol, (h, c[h], ref, sl, tol)
+
+
+@pytest.mark.parametrize("beta", [4.0, 64.0])
+def test_solve_on_a_flat_stretch_ends_where_bisection_ends(beta):
+    """Where g equals the target over a stretch (two clusters of scores far apart, the
+    density one cluster's share; or every score counted, density the whole), every point
+    of it is a root, and bisection's is the stretch's lower end: where the nearer cluster
+    below still adds a rounding of g, anything from a quarter to a whole one with the order
+    of g's additions (a factor of 4 in that cluster's exponential: log 4 / beta).  Heads 2
+    and 3 count every score: the bracket's lower end."""
+    lo, hi, nb = -8.0, 24.0, 512
+    hist = np.zeros((4, nb), dtype=np.int64)
+    hist[0, 10], hist[0, 500] = 1 << 40, 1 << 40
+    hist[1, 0:4], hist[1, 508:512] = 3 << 38, 1 << 38
+    hist[2, 256] = 1 << 44
+    hist[3, :] = 1 << 36
+    dens = np.array([1 << 40, 4 << 38, 1 << 44, nb << 36], dtype=np.int64)
+    c, target = _solve_counts(hist, dens, beta=beta, lo=lo, hi=hi)
+    for h in range(4):
+        ref = oracle.calib_solve(hist[h].astype(np.float64), lo, hi, beta, float(target[h]))
+        tol = 1e-9 / beta + abs(ref) * U + (math.log(4.0) / beta if h < 2 else 0.0)
+        assert abs(c[h] - ref) <= tol, (h, c[h], ref)
