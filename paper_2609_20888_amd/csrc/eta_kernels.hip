@@ -1225,7 +1225,8 @@ __device__ __forceinline__ void attend_f32(const float* __restrict__ kb, const f
     float sc[G], p[G];
 #pragma unroll
     for (int h = 0; h < G; ++h)
-      sc[h] = gated<DENSE>(dot[h], valid && ((bits >> h) & 1u), ung, 1.0f, nbs, bt_s[h]);
+      // (an open gate passes any score, -inf too, where the gate's own sum is NaN)
+      sc[h] = gated<DENSE>(dot[h], valid && ((bits >> h) & 1u), ung || bt_s[h] == kNegInf, 1.0f, nbs, bt_s[h]);
     ss.step(sc, p);
 #pragma unroll
     for (int h = 0; h < G; ++h) p_s[lane][h] = p[h];

@@ -192,6 +192,20 @@ def test_decode_moving_reference_and_tails(G, d, dt, tail, beta):
         say(compare(wl, g, orc, tau_o, np_inputs=np_in, union_counts=g.union_counts))
 
 
+@pytest.mark.parametrize("d,G", [(64, 1), (128, 4)])
+def test_fp32_open_gate_takes_a_minus_infinite_score(d, G):
+    """tau = -inf opens the gate for every score, -inf (a key that overflows to it) too:
+    that token weighs nothing, as with a key far below all others."""
+    wl = make_workload(B=1, Hq=2 * G, Hkv=2, d=d, block=64, seq_lens=[3 * 64 + 10],
+                       dtype=torch.float32, predictor=False, tau_const=float("-inf"), seed=d)
+    wl.q[..., 0] = wl.q[..., 0].abs() + 0.5
+    wl.k[0, :, -3, 0] = -1e6
+    orc, tau_o = run_oracle(wl)
+    wl.k[0, :, -3, 0] = float("-inf")          # (in the tail: no block record holds it)
+    for splits in (0, 1):
+        say(compare(wl, run_gpu(wl, num_splits=splits), orc, tau_o))
+
+
 def test_decode_fp32_query_on_bf16_cache():
     # fp32 q with bf16 K/V: the scores use the hi + lo bf16 split of q
     wl = make_workload(B=1, Hq=8, Hkv=2, d=128, block=64, seq_lens=[9000],
