@@ -1252,7 +1252,7 @@ __device__ __forceinline__ void attend_f32(const float* __restrict__ kb, const f
 // softmax, weights to LDS, p.V.  V is read in dwords (two dims per lane): a load
 // covers one row of 128 dims, or two rows of 64, so with D = 64 half a wavefront takes
 // the even tokens and half the odd ones and the halves are added at the end.
-template <int D, int G, bool DENSE>
+template <int D, int G, bool DENSE, bool PROP>
 struct Bf16Tile {
   static constexpr int DC = D / 8;               // 16-byte chunks per row = MFMAs per head quad
   static constexpr int NQ = G > 4 ? G / 4 : 1;   // head quads
@@ -1362,11 +1362,14 @@ struct Bf16Tile {
   template <typename TB, typename BITS>
   __device__ __forceinline__ void stream(int ntiles, TB tile_base, BITS tile_bits, SoftState<G, 2>& ss) const {
     if (ntiles <= 0) return;
-    // parts of V: a part of the next tile is requested when this tile's is consumed.  One
-    // part for the dense baseline (32 x 64K ragged, d = 128: 865 us with four, 859 with two,
-    // 854 with one), two where the gate leaves longer gaps (32 ragged sequences, 10%:
-    // 353.5 us with four, 350.4 with two; 512K equal)
-    constexpr int NCK = DENSE ? 1 : 2;
+    // parts of V: a part of the next tile is requested when this tile's is consumed.  Two
+    // where the gate leaves longer gaps (32 ragged sequences, 10%: 353.5 us with four,
+    // 350.4 with two; 512K equal) and for the dense baseline's uniform plan of up to four
+    // heads, one workgroup per compute unit (one 64K sequence, 16/4 heads, d = 128: 31.7 us
+    // with one, 29.5 with two, 29.2 with four; 512K: 174, 168, 176); one for eight heads,
+    // whose p.V is longer (4 x 64K, 64/8: 187, 192, 195), and for the dense plan by length,
+    // two workgroups per unit (8 x 64K ragged, 32/8: 240, 243).
+    constexpr int NCK = DENSE && (PROP || G == 8) ? 1 : 2;
     constexpr int NR = NV / NCK;
     uint4 kr[DC];
     uint32_t vr[NV];
@@ -1781,7 +1784,7 @@ __global__ __launch_bounds__(64 * kSplitWaves) void split_kernel(SplitArgs a) {
   // row 4 tg + h of A holds query head h in the k-slots of lane group tg: lanes of
   // other groups read zeros
   const bool diag = ((lane & 15) >> 2) == (lane >> 4);
-  [[maybe_unused]] const Bf16Tile<D, G, DENSE> bt{
+  [[maybe_unused]] const Bf16Tile<D, G, DENSE, PROP> bt{
       reinterpret_cast<const uint16_t*>(kb), reinterpret_cast<const uint16_t*>(vb), g.st,
       diag ? qa_s + (lane & 3) * DC : qz_s, use_lo, bt_s, p_s[w], scale * kLog2e,
       -a.beta * (scale * kLog2e), self_t, lane};
