@@ -238,16 +238,37 @@ SplitPlan plan_splits(const Geom& g, int num_splits) {
 // wavefront (a uniform count left the short sequences' workgroups idle, and 2048 tokens or
 // more to each: 8 ragged sequences up to 32K, 16/4 heads, d = 128: 79 -> 67 us; 2 x 4000
 // tokens, 8/2 heads: 69 -> 17 with 256 tokens, 20 with 512, 31 with 1024; equal from 15K
-// tokens on).
+// tokens on).  Four per group (at least 512 in all), eight for long caches and for fp32 ones
+// from 256 groups on (16/4 heads, d = 128, ragged, us with four and eight: 32 x 2048 tokens
+// 29.5, 33.9; 64 x 8K 130, 129; 64 x 16K 247, 236; fp32, 64 x 8K 313, 288).
 constexpr int kDenseTokens = 256;
 
 int dense_prop_workgroups(const Geom& g) {
   const int64_t BG = (int64_t)g.B * g.Hkv;
-  int64_t W = 8 * BG;
+  int64_t W = (g.cap >= 16384 || (g.kv_dtype == ETA_DT_F32 && BG >= 256) ? 8 : 4) * BG;
   W = W < kPropSplits ? kPropSplits : (W > kPropMaxSplits ? kPropMaxSplits : W);
   const int64_t most = BG * (g.cap / kDenseTokens > 1 ? g.cap / kDenseTokens : 1);
   if (W > most) W = most;
   return (int)(W < BG ? BG : W);
+}
+
+// The capacity from which a batch's groups are split at all: below it one workgroup per
+// group writes the output itself, without the plan's scan of the lengths, the partials and
+// the combine (4 to 7 us in all, and more where the groups alone fill the 256 compute
+// units).  One against four per group, us, 16/4 heads, d = 128, equal lengths / ragged:
+//    16 groups:  512 tokens 13.3 / 14.6, 14.2 / 19.4;  768: 15.5 / 18.1, 13.8 / 16.9
+//   128 groups: 1024 tokens 20.7 / 22.4, 21.2 / 21.3; 2048: 35 / 39, 32 / 30
+//   256 groups: 4096 tokens 80 / 74, 94 / 72;         8192: 165 / 148, 177 / 130
+//   512 groups: 4096 tokens 163 / 138, 179 / 130;     8192: 316 / 268, 339 / 228
+// Rows of 64 dims of one or two heads take half the time a tile, so twice the tokens (one
+// head, 16 groups of 1024: 9.6, 12.4; 128 groups of 2048: 16.6 / 16.0, 17.7 / 16.2); fp32
+// caches longer, so fewer (64 groups of 768: 27.6, 21.7; 256 of 2048: 91, 93 with eight,
+// of 4096: 175, 162).
+int64_t dense_split_from(const Geom& g) {
+  const int64_t BG = (int64_t)g.B * g.Hkv;
+  if (g.kv_dtype == ETA_DT_F32) return BG < 128 ? 768 : BG < 256 ? 1024 : 3072;
+  const int64_t t = BG < 128 ? 896 : BG < 256 ? 1536 : BG < 512 ? 6144 : 8192;
+  return g.G * g.D <= 128 ? 2 * t : t;
 }
 
 int dense_splits(const Geom& g, int num_splits) {
@@ -255,7 +276,7 @@ int dense_splits(const Geom& g, int num_splits) {
   const int64_t BG = (int64_t)g.B * g.Hkv;
   // (the kernel adds the groups' tiles in 32 bits)
   if (g.B > 1 && BG <= kPropMaxGroups && BG * (g.cap / 64 + 1) < (int64_t(1) << 30))
-    return dense_prop_workgroups(g) > BG ? 0 : 1;
+    return g.cap >= dense_split_from(g) ? 0 : 1;
   return default_splits(g);
 }
 

@@ -274,6 +274,37 @@ static void decode_geometry(int B, int Hq, int Hkv, int d, int b, int64_t cap, i
   std::free(ws);
 }
 
+// The dense plan for a call's num_splits = 0: 0 by length, else splits per group.
+static int dense_plan(int B, int Hq, int Hkv, int d, int64_t cap, int dt) {
+  eta::Geom g{};
+  g.B = B;
+  g.Hq = Hq;
+  g.Hkv = Hkv;
+  g.D = d;
+  g.BS = 64;
+  g.G = Hq / Hkv;
+  g.kv_dtype = dt;
+  g.cap = cap;
+  g.ncap = cap / 64 > 1 ? cap / 64 : 1;
+  return eta::dense_splits(g, 0);
+}
+
+// A plan by length only where splitting a group pays; its workgroups.
+static void dense_plans() {
+  const int BF = ETA_DT_BF16, F32 = ETA_DT_F32;
+  struct { int B, Hq, Hkv, d; int64_t cap; int dt, want; } cases[] = {
+      {4, 16, 4, 128, 512, BF, 1},     {4, 16, 4, 128, 895, BF, 1},     {4, 16, 4, 128, 896, BF, 0},
+      {2, 8, 8, 64, 1024, BF, 1},      {2, 8, 8, 64, 1792, BF, 0},      {32, 16, 4, 128, 1024, BF, 1},
+      {32, 16, 4, 128, 2048, BF, 0},   {64, 16, 4, 128, 2048, BF, 1},   {64, 16, 4, 128, 8192, BF, 0},
+      {128, 32, 4, 64, 2048, BF, 1},   {128, 32, 4, 64, 8192, BF, 0},   {16, 16, 4, 128, 768, F32, 0},
+      {64, 16, 4, 128, 2048, F32, 1},  {64, 16, 4, 128, 4096, F32, 0},  {1025, 1, 1, 128, 2048, BF, 1}};
+  for (const auto& c : cases) {
+    const int S = dense_plan(c.B, c.Hq, c.Hkv, c.d, c.cap, c.dt);
+    CHECK(S == c.want, "dense plan B=%d %d/%d d=%d cap=%lld: %d splits", c.B, c.Hq,
+          c.Hkv, c.d, (long long)c.cap, S);
+  }
+}
+
 static void invalid_calls() {
   eta_kv_desc_t k = desc(2, 16, 4, 128, 64, 4096);
   eta_decode_params_t p = params();
@@ -382,6 +413,7 @@ int main() {
     for (int64_t cap : {1, 63, 64, 4097})
       for (int S : {0, 1})
         for (int64_t extra : {1, 65}) decode_geometry(B, 16, 4, 128, 64, cap, S, extra);
+  dense_plans();
   invalid_calls();
   other_entry_points();
   if (failures) {

@@ -330,6 +330,10 @@ DENSE_PLAN = {
     "odd_heads_300_groups": (100, 3, 3, 64, 64, 600, [(37 * i) % 601 for i in range(100)], torch.bfloat16),
     "past_the_group_table": (520, 2, 2, 64, 64, 300, [(53 * i) % 301 for i in range(520)], torch.bfloat16),
     "one_split_per_group": (4, 4, 1, 128, 64, 500, [500, 256, 255, 3], torch.bfloat16),
+    "one_workgroup_of_3_tiles": (3, 8, 2, 128, 64, 895, [895, 0, 640], torch.bfloat16),
+    "split_from_896_tokens": (3, 8, 2, 128, 64, 896, [896, 1, 700], torch.bfloat16),
+    "fp32_300_groups_by_length": (300, 2, 1, 64, 64, 3072, [(37 * i) % 601 for i in range(299)] + [3072],
+                                  torch.float32),
 }
 
 
