@@ -205,6 +205,31 @@ int default_splits(const Geom& g) {
   return (int)S;
 }
 
+// Whether a workgroup takes 32 blocks (else 4, one per wavefront).  With 32 the records leave
+// as whole 64- to 128-byte rows; with 4 up to eight times the workgroups start, and short ones
+// (2 x 32K tokens, 2 kv heads, d = 128: 57 -> 11 us).  32 wins where K alone fills the card
+// several times over (equal at 400 MiB; 512 MiB, 128-token blocks: 98 us against 105; fp32
+// rows of 128 dims: 4 takes 0.92 to 0.99 of 32's time at 320 MiB, 1.02 to 1.12 at 384), and
+// below that as soon as its workgroups come out at one and a half to two per compute unit.
+// 4's time over 32's by the number of workgroups of 32 (fp32 / fp16 records, 4 heads):
+//   bf16, d = 64, b = 64:    256: 0.78 / 0.70, 448: 0.90 / 0.87, 512: 1.11 / 0.99, 768: 1.08
+//   bf16, d = 64, b = 128:   256: 0.88 / 0.86, 384: 0.99 / 0.97, 448: 1.10 / 1.08, 512: 1.16 / 1.12
+//   bf16, d = 128, b = 64:   256: 1.02 / 0.93, 384: 1.05 / 1.00, 448: 1.17 / 1.11, 512: 1.31 / 1.24
+//   fp32, d = 64, b = 64:    192: 0.95 / 0.91, 256: 1.18 / 1.11, 512: 1.22 / 1.15, 768: 1.13 / 1.12
+//   envelope, d = 128:       384: 0.95, 448: 1.04, 512: 1.20 (fp32, d = 64: 0.88, 0.98, 1.08)
+// Records of 8 bits leave in quarter rows and their conversion takes vector work, and the
+// envelope of 64-dim bf16 rows computes longer: there 4 wins up to 400 MiB (0.73 to 0.98 at
+// 448 and 512), except for 8-bit records of fp32 64 x 64 blocks (448: 1.05).
+bool summary_wide(const Geom& g, int64_t nblk, int sub_block) {
+  const bool f32 = g.kv_dtype == ETA_DT_F32, fp8 = g.stat_dtype == ETA_DT_FP8;
+  const int64_t blocks = nblk * g.Hkv * g.B, row = g.D * (f32 ? 4 : 2);
+  if (blocks * g.BS * row >= (int64_t(f32 && g.D == 128 && !fp8 ? 360 : 400) << 20)) return true;
+  const bool small_f32 = f32 && g.D == 64 && g.BS == 64;
+  if (!f32 && (fp8 || (sub_block > 0 && g.D == 64))) return false;
+  const int64_t from = fp8 || sub_block > 0 ? 448 : small_f32 ? 256 : g.BS * row < 16384 ? 512 : 384;
+  return nblk >= 32 && blocks >= 32 * from;
+}
+
 // Split layout of a decode call.  One sequence (or a tile count table too large
 // for the split kernel's LDS): S splits per kv head, num_splits or the default
 // (one workgroup per compute unit for one sequence).  Several sequences: W =

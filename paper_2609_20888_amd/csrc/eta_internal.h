@@ -70,6 +70,8 @@ int default_splits(const Geom& g);
 // plan, and that plan's workgroups.
 int dense_splits(const Geom& g, int num_splits);
 int dense_prop_workgroups(const Geom& g);
+// Whether a workgroup of the index build takes 32 blocks, of nblk per (sequence, kv head).
+bool summary_wide(const Geom& g, int64_t nblk, int sub_block);
 
 struct DecodeCfg {
   float beta, z, offset_a;

@@ -262,7 +262,7 @@ __device__ __forceinline__ int wave_incl_scan(int x) {
 // groups: taken for two coordinates per row swap (32 x 64K tokens, 4 heads, d = 64, b = 64,
 // sub-blocks of 4: 290 -> 223 us; of 8: 320 -> 220).
 //
-// NB: 32 for large caches, else 4 (see launch_summaries).
+// NB: 32 for large caches, else 4 (summary_wide).
 
 // Sum over the aligned group of N lanes (N in 8, 16, 32) that holds one row;
 // every lane of the group ends with the same value.
@@ -2404,15 +2404,7 @@ hipError_t launch_summaries(const Geom& g, const void* k, const int32_t* seq_len
                             const eta_summary_t& s, hipStream_t stream, LaunchHook hook) {
   const int64_t nblk = prev_lens != nullptr ? max_new_blocks : g.cap / g.BS;
   if (nblk <= 0) return hipSuccess;
-  // Blocks per workgroup: with 32 the records leave as whole 64- to 128-byte rows, but
-  // one block per wavefront (4) starts up to eight times the workgroups and makes them
-  // short.  32 wins where K alone fills the card several times over (512 MiB of K, 128-token
-  // blocks: 98 us against 105 with 4; 1 GiB, 64-token blocks: 203 against 216), 4 below
-  // (2 x 32K tokens, 2 kv heads, d = 128: 57 -> 11 us; 8 x 32000, 4 heads, d = 64,
-  // flat 31 -> 29, envelope of 4: 39 -> 32, and
-  // 62 before its sub-block sums took the transposed route); equal at 397 MB.
-  const int64_t kbytes = nblk * g.BS * g.Hkv * g.B * g.D * (g.kv_dtype == ETA_DT_F32 ? 4 : 2);
-  const bool nb32 = kbytes >= (int64_t(400) << 20);
+  const bool nb32 = summary_wide(g, nblk, sub_block);
   const int nb = nb32 ? 32 : 4;
   dim3 grid((unsigned)((nblk + nb - 1) / nb), g.Hkv, g.B);
   int sub_log2 = 0;

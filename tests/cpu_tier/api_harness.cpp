@@ -305,6 +305,33 @@ static void dense_plans() {
   }
 }
 
+// Blocks per workgroup of the index build: both sides of each line.
+static void summary_widths() {
+  const int BF = ETA_DT_BF16, F32 = ETA_DT_F32, F16 = ETA_DT_F16, FP8 = ETA_DT_FP8;
+  struct { int B, Hkv, d, b; int64_t nblk; int dt, rec, sub; bool want; } cases[] = {
+      {1, 4, 64, 64, 4092, BF, F32, 0, false},   {1, 4, 64, 64, 4096, BF, F32, 0, true},
+      {1, 8, 64, 128, 1532, BF, F32, 0, false},  {1, 8, 64, 128, 1536, BF, F32, 0, true},
+      {2, 4, 128, 64, 1536, BF, F16, 0, true},   {1, 4, 128, 64, 3580, BF, F16, 8, false},
+      {1, 4, 128, 64, 3584, BF, F16, 8, true},   {1, 4, 64, 64, 8192, BF, F16, 4, false},
+      {1, 4, 64, 64, 12800, BF, F16, 4, true},   {1, 4, 128, 128, 2048, BF, F16, 0, false},
+      {1, 4, 128, 128, 3199, BF, FP8, 0, false}, {1, 4, 128, 128, 3200, BF, FP8, 0, true},
+      {1, 4, 64, 64, 2047, F32, F32, 0, false},  {1, 4, 64, 64, 2048, F32, F32, 0, true},
+      {1, 4, 64, 64, 3583, F32, FP8, 0, false},  {1, 4, 64, 64, 3584, F32, FP8, 0, true},
+      {1, 4, 128, 128, 1439, F32, F32, 0, false}, {1, 4, 128, 128, 1440, F32, F32, 0, true},
+      {512, 64, 128, 64, 1, BF, F32, 0, true},   {256, 64, 128, 64, 1, BF, F32, 0, false}};
+  for (const auto& c : cases) {
+    eta::Geom g{};
+    g.B = c.B;
+    g.Hkv = c.Hkv;
+    g.D = c.d;
+    g.BS = c.b;
+    g.kv_dtype = c.dt;
+    g.stat_dtype = c.rec;
+    CHECK(eta::summary_wide(g, c.nblk, c.sub) == c.want, "index build B=%d Hkv=%d d=%d b=%d, %lld blocks", c.B,
+          c.Hkv, c.d, c.b, (long long)c.nblk);
+  }
+}
+
 static void invalid_calls() {
   eta_kv_desc_t k = desc(2, 16, 4, 128, 64, 4096);
   eta_decode_params_t p = params();
@@ -414,6 +441,7 @@ int main() {
       for (int S : {0, 1})
         for (int64_t extra : {1, 65}) decode_geometry(B, 16, 4, 128, 64, cap, S, extra);
   dense_plans();
+  summary_widths();
   invalid_calls();
   other_entry_points();
   if (failures) {

@@ -48,6 +48,31 @@ ENVELOPE_CASES = [
 ]
 
 
+@pytest.mark.parametrize("dt,d,b,sub,n_cap", [
+    (torch.bfloat16, 64, 64, 0, 16384), (torch.bfloat16, 128, 64, 8, 14336),
+    (torch.bfloat16, 64, 128, 0, 12288), (torch.float32, 64, 64, 0, 8192)])
+@pytest.mark.parametrize("stat", [torch.float32, torch.float16])
+def test_wide_and_narrow_workgroups_write_the_same_records(stat, dt, d, b, sub, n_cap):
+    """The same keys in a short cache (4 blocks per workgroup) and in one long enough for 32
+    (n_cap blocks in all, two heads): equal records, nothing past the last full block."""
+    n = 75
+    T, cap = n * b + 11, n_cap // 2 * b
+    gen = torch.Generator(device="cuda").manual_seed(d + b)
+    k = (torch.randn(1, 2, T, d, generator=gen, device="cuda") + 1.0).to(dt)
+    big = torch.zeros(1, 2, cap, d, device="cuda", dtype=dt)
+    big[:, :, :T] = k
+    sl = torch.tensor([T], dtype=torch.int32, device="cuda")
+    a = eta.build_block_summaries(k, sl, b, sub_block=sub, stat_dtype=stat)
+    w = eta.Summaries.empty(1, 2, d, cap // b, "cuda", stat)
+    for t in (w.mu, w.sigma, w.max_norm):
+        t.fill_(-7.0)
+    eta.build_block_summaries(big, sl, b, out=w, sub_block=sub)
+    torch.cuda.synchronize()
+    for x, y in zip((a.mu, a.sigma, a.max_norm), (w.mu, w.sigma, w.max_norm)):
+        assert torch.equal(x[..., :n], y[..., :n])
+        assert torch.all(y[..., n:] == -7.0)
+
+
 @pytest.mark.parametrize("case", range(len(ENVELOPE_CASES)))
 def test_envelope_matches_oracle(case):
     B, Hkv, d, b, lens, dt, subs = ENVELOPE_CASES[case]
