@@ -17,6 +17,7 @@
 
 static int failures = 0;
 static int launches = 0;
+static int dense_by_length = 0;     // dense decodes that took the plan by length
 #define CHECK(c, ...)                                                 \
   do {                                                                \
     if (!(c)) {                                                       \
@@ -172,8 +173,17 @@ hipError_t launch_dense(const Geom& g, int S, int, const void*, const void*, con
                         const int32_t*, void*, const DecodeWs& ws, hipStream_t stream, LaunchHook hook) {
   ++launches;
   bracket(hook, ETA_KERNEL_DENSE_SPLIT, stream);
-  const size_t BH = (size_t)g.B * g.Hq;
-  std::vector<Region> rs = {{ws.part_ml, BH * S * 8}, {ws.part_acc, BH * S * g.D * 4}};
+  // S = 0: the plan by length, whose kernel needs a workgroup for every group, groups within
+  // its table and the groups' tiles in 32 bits
+  const size_t BG = (size_t)g.B * g.Hkv, W = S > 0 ? BG * S : (size_t)dense_prop_workgroups(g);
+  std::vector<Region> rs = {{ws.part_ml, W * g.G * 8}, {ws.part_acc, W * g.G * g.D * 4}};
+  if (S == 0) {
+    ++dense_by_length;
+    CHECK(W >= BG && W <= INT32_MAX, "dense: %zu workgroups for %zu groups", W, BG);
+    CHECK(g.B > 1 && BG <= kPropMaxGroups && (int64_t)BG * (g.cap / 64 + 1) < INT32_MAX,
+          "dense: plan by length for %zu groups of %lld tokens", BG, (long long)g.cap);
+    rs.push_back({ws.plan, BG * 8});
+  }
   fill_and_check(rs, "dense");
   return hipSuccess;
 }
@@ -434,6 +444,11 @@ int main() {
   decode_geometry(1, 16, 4, 128, 64, (int64_t)2048 * 64 * 64, 0);   // 2048 screening tiles
   decode_geometry(256, 32, 8, 128, 64, 65536, 0);                   // 2048 groups: uniform plan
   decode_geometry(32, 32, 8, 128, 64, 65536, 0);                    // proportional, 4096 counts
+  // dense: capacities below, between and past one and two tiles per wavefront; the largest
+  // group table and one group past it
+  for (int64_t cap : {255, 256, 511, 512, 895, 896, 1024, 8192}) decode_geometry(3, 8, 2, 128, 64, cap, 0);
+  for (int B : {1024, 1025})
+    for (int64_t cap : {255, 512, 8192, 65536}) decode_geometry(B, 4, 1, 64, 64, cap, 0);
   // summaries larger than the cache: one block past, a tile past, and T < b with a
   // one-block summary (capacity_tokens / block_size = 0)
   for (int B : {1, 8})
@@ -444,6 +459,7 @@ int main() {
   summary_widths();
   invalid_calls();
   other_entry_points();
+  CHECK(dense_by_length > 50, "%d dense plans by length", dense_by_length);
   if (failures) {
     std::fprintf(stderr, "%d check(s) failed\n", failures);
     return 1;

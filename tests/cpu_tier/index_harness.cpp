@@ -225,6 +225,12 @@ int main() {
       for (auto& x : work) x = 0;
       work[BG - 1] = 262145;
       check_plan(work, W);                                          // one long union
+      // dense: every block of a sequence and its tail, the kv heads of a sequence alike
+      for (int x = 0; x < BG; ++x) {
+        const int64_t len = (int64_t)(rng() % 8193);
+        work[x] = x % 4 == 0 ? group_work((int)(len / 64), 1, len, 64) : work[x - 1];
+      }
+      check_plan(work, W);
     }
   }
   // union lists: T < b (no tile counted), one tile, ragged, the largest table
