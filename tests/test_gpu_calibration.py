@@ -64,8 +64,11 @@ CASES = [
 
 @pytest.mark.parametrize("case", range(len(CASES)))
 def test_calibration_matches_oracle(case):
-    N, Hq, Hkv, T, d, beta, lo, hi, nb = CASES[case]
-    cs = calib_stream(N=N, Hq=Hq, Hkv=Hkv, T=T, d=d, seed=100 + case, device="cuda")
+    _check_calibration(*CASES[case], seed=100 + case)
+
+
+def _check_calibration(N, Hq, Hkv, T, d, beta, lo, hi, nb, *, seed):
+    cs = calib_stream(N=N, Hq=Hq, Hkv=Hkv, T=T, d=d, seed=seed, device="cuda")
     hist, dens, c, target = _gpu_calibrate(cs, beta=beta, lo=lo, hi=hi, nb=nb)
     qn, kn = as_numpy(cs.q), as_numpy(cs.k)
     tau = cs.tau.cpu().numpy().astype(np.float64)
@@ -93,7 +96,7 @@ def test_calibration_matches_oracle(case):
         assert resid <= tol, (h, resid, tol)
         worst = max(worst, resid)
     c_orc = np.array([oracle.calib_solve(r.hist[h], lo, hi, beta, r.target[h]) for h in range(Hq)])
-    say(f"[gpu] calibration case {case}: max |c_gpu - c_oracle| {np.max(np.abs(c - c_orc)):.2e}, "
+    say(f"[gpu] calibration {N}x{T}, {Hq}/{Hkv}, d={d}: max |c_gpu - c_oracle| {np.max(np.abs(c - c_orc)):.2e}, "
         f"max g residual {worst:.2e}, ambiguous mass {amb.max():.2e}")
 
 
@@ -122,11 +125,7 @@ def test_constant_dynamic_threshold_is_recovered():
 def test_calibration_block_edges(T, N, Hq, Hkv, d, nb):
     """Steps around the 16-query groups, 64-query blocks and 256-query workgroups; bins
     around the solver's 1024 threads."""
-    CASES.append((N, Hq, Hkv, T, d, 4.0, -6.0, 10.0, nb))
-    try:
-        test_calibration_matches_oracle(len(CASES) - 1)
-    finally:
-        CASES.pop()
+    _check_calibration(N, Hq, Hkv, T, d, 4.0, -6.0, 10.0, nb, seed=100 + len(CASES))
 
 
 def test_calibration_adds_up_over_calls_with_several_workgroups_per_head():

@@ -75,9 +75,12 @@ def test_wide_and_narrow_workgroups_write_the_same_records(stat, dt, d, b, sub, 
 
 @pytest.mark.parametrize("case", range(len(ENVELOPE_CASES)))
 def test_envelope_matches_oracle(case):
-    B, Hkv, d, b, lens, dt, subs = ENVELOPE_CASES[case]
+    _check_envelope(*ENVELOPE_CASES[case], seed=40 + case)
+
+
+def _check_envelope(B, Hkv, d, b, lens, dt, subs, *, seed):
     wl = make_workload(B=B, Hq=Hkv, Hkv=Hkv, d=d, block=b, seq_lens=lens, dtype=dt,
-                       planted={"frac": 0.1}, predictor=False, tau_const=1.0, seed=40 + case)
+                       planted={"frac": 0.1}, predictor=False, tau_const=1.0, seed=seed)
     dev = torch.device("cuda")
     k = wl.k.to(dev)
     sl = torch.tensor(lens, dtype=torch.int32, device=dev)
@@ -205,11 +208,7 @@ def test_decode_on_envelope_summaries_matches_oracle(sub, lwb):
                                      (64, 128, 128), (128, 64, 64), (128, 128, 2)])
 def test_envelope_sub_block_edges(d, b, sub):
     """Sub-blocks below, at and above the row groups that one load covers."""
-    ENVELOPE_CASES.append((2, 1, d, b, [b * 9 + 5, b * 2], torch.bfloat16, (sub,)))
-    try:
-        test_envelope_matches_oracle(len(ENVELOPE_CASES) - 1)
-    finally:
-        ENVELOPE_CASES.pop()
+    _check_envelope(2, 1, d, b, [b * 9 + 5, b * 2], torch.bfloat16, (sub,), seed=40 + len(ENVELOPE_CASES))
 
 
 @pytest.mark.parametrize("d,b,sub,rec", [(128, 128, 0, torch.float32), (128, 64, 4, torch.float16),

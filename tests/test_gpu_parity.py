@@ -363,6 +363,49 @@ def test_dense_decode_plan_shapes(name):
             assert np.max(np.abs(o[bb, h] - ref)) <= tol * np.max(np.abs(ref)), (bb, h)
 
 
+def _strided(t, layout):
+    """t's values in a [B][T][Hkv][d] cache, or with rows of d + 8 elements; NaN between."""
+    B, H, T, d = t.shape
+    if layout == "interleaved":
+        return t.permute(0, 2, 1, 3).contiguous().permute(0, 2, 1, 3)
+    big = torch.full((B, H, T, d + 8), float("nan"), dtype=t.dtype, device=t.device)
+    big[..., :d] = t
+    return big[..., :d]
+
+
+@pytest.mark.parametrize("layout", ["interleaved", "padded"])
+@pytest.mark.parametrize("G,d,b,dt,lens", [
+    (1, 64, 64, torch.bfloat16, [3001]), (4, 64, 128, torch.bfloat16, [2900, 77]),
+    (8, 64, 64, torch.bfloat16, [1000, 2500]), (2, 128, 64, torch.bfloat16, [5003]),
+    (4, 128, 128, torch.bfloat16, [4000, 129]), (2, 64, 64, torch.float32, [900, 2049]),
+    (4, 128, 64, torch.float32, [1500])])
+def test_strided_caches_give_the_contiguous_results(G, d, b, dt, lens, layout):
+    """Any token and head stride (multiples of 16 bytes): the index, sparse decode (the query
+    in the cache's type and in fp32) and dense decode are those of a contiguous cache, bit for
+    bit, with the library's splits and with one."""
+    wl = make_workload(B=len(lens), Hq=2 * G, Hkv=2, d=d, block=b, seq_lens=lens, dtype=dt,
+                       planted={"frac": 0.2}, predictor=False, tau_const=0.5, seed=d + G)
+    dev = torch.device("cuda")
+    sl = torch.tensor(lens, dtype=torch.int32, device=dev)
+    k, v = wl.k.to(dev), wl.v.to(dev)
+    ks, vs = _strided(k, layout), _strided(v, layout)
+    assert ks.stride(2) != d
+    tau = torch.full((len(lens), 2 * G), 0.5, device=dev)
+    s, ss = (eta.build_block_summaries(x, sl, b, num_q_heads=2 * G) for x in (k, ks))
+    n = min(lens) // b
+    assert torch.equal(s.mu[..., :n], ss.mu[..., :n]) and torch.equal(s.sigma[..., :n], ss.sigma[..., :n])
+    for q in (wl.q.to(dev), wl.q.to(dev).float()):
+        for splits in (0, 1):
+            p = eta.decode_params(beta=4.0, z=1.0, rescue_window=16, num_splits=splits)
+            a = eta.decode(q, k, v, sl, s, tau, block_size=b, params=p)
+            c = eta.decode(q, ks, vs, sl, s, tau, block_size=b, params=p)
+            assert torch.equal(a.mask, c.mask) and torch.equal(a.out, c.out)
+            assert torch.isfinite(c.out).all() and c.out.abs().max() > 0
+            e = eta.dense_decode(q, k, v, sl, block_size=b, num_splits=splits)
+            f = eta.dense_decode(q, ks, vs, sl, block_size=b, num_splits=splits)
+            assert torch.equal(e, f) and torch.isfinite(f).all()
+
+
 # ------------------------------------------------------------------ full-size workloads
 
 def test_config1_full():
