@@ -1179,7 +1179,10 @@ struct SoftState {
 // fp32 K/V: scores on the vector ALUs.  A split of a short cache is one tile, all
 // latency: K and the first half of V are requested together, the rest of V two chunks
 // ahead (one 4K sequence, d = 64: split decode 7.8 -> 6.6 us; two 16K sequences, 32/8
-// heads, d = 128: step 51.8 -> 44.8 us).
+// heads, d = 128: step 51.8 -> 44.8 us).  At d = 128, four heads, the registers leave two
+// wavefronts per SIMD, not five; long and batched caches gained all the same (steps of
+// 1 x 128K tokens, 16/4 heads: 60 -> 42 us, 8 x 32K 90 -> 83, 32 ragged x 8K 64 -> 64; dense
+// 8 x 32K 211 -> 210).
 template <int D, int G, bool DENSE>
 __device__ __forceinline__ void attend_f32(const float* __restrict__ kb, const float* __restrict__ vb,
                                            int64_t st, int64_t t0, int nvalid, uint32_t bits,
@@ -1539,7 +1542,7 @@ __global__ __launch_bounds__(64 * kSplitWaves) void split_kernel(SplitArgs a) {
     ntl = __builtin_amdgcn_readlane(wave_incl_scan(ntl), 63);
     if (lane == 63) wsum_s[w] = incl;
     if (lane == 0) wtail_s[w] = ntl;
-    if (tid == 0) own_s[0] = -1;            // no group yet (set after two more barriers)
+    if (tid == 0) own_s[0] = -1;            // no group yet (set three barriers on, dense: two)
     __syncthreads();
     int woff = 0, tot = 0, ntails = 0;
 #pragma unroll
@@ -1957,9 +1960,10 @@ __global__ __launch_bounds__(64 * kSplitWaves) void split_kernel(SplitArgs a) {
 // up to the same integers.  Only a group's diagonal tile is masked; rows past the
 // last step carry zero weight.  The workgroup's four blocks are neighbours (equal
 // causal ranges), the longest first.
-// Bound by the vector unit (17 instructions, 19 issue slots per score) and, behind it,
-// the LDS atomics (60% busy): eight sequences of 2048 steps, 32/8 heads, d = 128
-// (537 M causal pairs): 2.11 -> 0.37 ms against one workgroup per (head, sequence) that
+// Bound by the vector unit (17.4 instructions, 19.5 issue slots per score, 88% of the busy
+// time) and, behind it, the LDS (56%): eight sequences of 2048 steps, 32/8 heads, d = 128
+// (537 M causal pairs), with the solve, calls in a row: 2.29 -> 0.35 ms (accumulation alone
+// 0.35 to 0.40 in a kernel trace) against one workgroup per (head, sequence) that
 // loaded each tile of keys for one 16-query group and masked every tile.
 // calib_solve_kernel: one workgroup per head, safeguarded Newton iteration in
 // fp64 on the histogram's density function with fixed-order block reductions.

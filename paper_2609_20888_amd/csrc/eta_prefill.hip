@@ -43,10 +43,10 @@ namespace {
 // before it (16x16x32, scores, softmax and p.V one after the other): 16K tokens,
 // 32/8 heads, d = 128: 3.34 -> 2.48 ms (659 -> 887 TFLOP/s); 2048 tokens, 128
 // heads, d = 64: 269 -> 131 us, d = 128: 333 -> 194 us, where the workgroup order
-// below also evens out the XCDs.  Tried: 64-key units (all 256 registers and
-// spills; 2% slower without); eight wavefronts sharing the tiles, 256 rows (half the L2
-// reads, but both wavefronts of a SIMD then wait at one barrier: 1% faster at 16K, 18%
-// slower at 2000 tokens).
+// below also evens out the XCDs.  Tried: 64-key units (all 256 registers, no faster; 3.7
+// ms with p.V carried into the next unit, which spills); eight wavefronts sharing the
+// tiles, 256 rows (half the L2 reads, but both wavefronts of a SIMD then wait at one
+// barrier: 1% faster at 16K, 18% slower at 2000 tokens).
 
 constexpr int kPfQ = 128;    // query rows per workgroup (32 per wavefront)
 constexpr int kPfK = 64;     // keys per block
@@ -101,7 +101,9 @@ __global__ __launch_bounds__(256, 2) void prefill_kernel(PrefillArgs a) {
   // query blocks go from the longest causal range to the shortest, all heads of
   // all sequences at each, so every XCD gets the same work; with a multiple of
   // eight heads an XCD takes Hq / 8 consecutive heads of every sequence, which
-  // share their K and V in its L2.
+  // share their K and V in its L2 as far as they are of one group: whole groups at
+  // 32/8 heads (four heads an XCD), half a group at 32/4, whose K and V two XCDs
+  // then read, and a quarter at 8/2.
   const uint32_t nqb = gridDim.x, NH = gridDim.y * gridDim.z;
   const uint32_t wg = blockIdx.x + nqb * (blockIdx.y + gridDim.y * blockIdx.z);
   const int qblk = (int)(nqb - 1 - wg / NH);
