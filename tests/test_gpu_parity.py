@@ -206,6 +206,38 @@ def test_fp32_open_gate_takes_a_minus_infinite_score(d, G):
         say(compare(wl, run_gpu(wl, num_splits=splits), orc, tau_o))
 
 
+def test_fp32_score_products_of_64_dims_are_summed_in_two_parts():
+    """Two tokens, open gates: the output is the first one's weight, from which its score's
+    error follows.  Scores near 35 in base-2 units, the terms all positive, the second token's
+    score a single product.  A chain of n additions that rises evenly to s rounds by half an
+    ulp of each partial sum, rms 2^-24 s sqrt(n / 3) / sqrt(3) at most: 5.6e-6 for one chain of
+    64 (4.2e-6 with partial sums spread over the ulp's binades), and two chains of 32 to s / 2
+    make half of it, 2.1e-6, and the last addition 1.1e-6: 2.4e-6 together.  Bound: 3.2e-6."""
+    dev = torch.device("cuda")
+    gen = torch.Generator().manual_seed(64)
+    B, H, d = 128, 8, 64
+    q = 0.5 + torch.rand(B, H, d, generator=gen)
+    k = torch.zeros(B, H, 64, d)
+    k[:, :, 0] = (0.5 + torch.rand(B, H, d, generator=gen)) * 2.9
+    s0 = (q.double() * k[:, :, 0].double()).sum(-1)
+    k[:, :, 1, 0] = (s0 / q[..., 0].double()).float()
+    v = torch.zeros(B, H, 64, d)
+    v[:, :, 0] = 1.0
+    sl = torch.full((B,), 2, dtype=torch.int32, device=dev)
+    k, v = k.to(dev), v.to(dev)
+    summ = eta.build_block_summaries(k, sl, 64, num_q_heads=H)
+    tau = torch.full((B, H), float("-inf"), device=dev)
+    out = eta.decode(q.to(dev), k, v, sl, summ, tau, block_size=64).out.cpu().double()[..., 0]
+    kc = k.cpu().double()
+    x = (q.double()[:, :, None] * kc[:, :, :2]).sum(-1) / math.sqrt(d) / math.log(2.0)
+    assert 25 < x[..., 0].min() and x[..., 0].max() < 50
+    w = torch.sigmoid((x[..., 0] - x[..., 1]) * math.log(2.0))
+    err = (out - w) / (w * (1 - w) * math.log(2.0))
+    rms = float(err.square().mean().sqrt())
+    say(f"[gpu] rms error of a base-2 score near 35: {rms:.2e}")
+    assert rms <= 3.2e-6
+
+
 def test_decode_fp32_query_on_bf16_cache():
     # fp32 q with bf16 K/V: the scores use the hi + lo bf16 split of q
     wl = make_workload(B=1, Hq=8, Hkv=2, d=128, block=64, seq_lens=[9000],
