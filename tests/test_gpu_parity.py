@@ -206,36 +206,55 @@ def test_fp32_open_gate_takes_a_minus_infinite_score(d, G):
         say(compare(wl, run_gpu(wl, num_splits=splits), orc, tau_o))
 
 
-def test_fp32_score_products_of_64_dims_are_summed_in_two_parts():
-    """Two tokens, open gates: the output is the first one's weight, from which its score's
-    error follows.  Scores near 35 in base-2 units, the terms all positive, the second token's
-    score a single product.  A chain of n additions that rises evenly to s rounds by half an
-    ulp of each partial sum, rms 2^-24 s sqrt(n / 3) / sqrt(3) at most: 5.6e-6 for one chain of
-    64 (4.2e-6 with partial sums spread over the ulp's binades), and two chains of 32 to s / 2
-    make half of it, 2.1e-6, and the last addition 1.1e-6: 2.4e-6 together.  Bound: 3.2e-6."""
+def _score_error_rms(d, kv_dtype):
+    """Two tokens, open gates, fp32 queries: the output is the first one's weight, from which
+    its score's error follows, the second token's score being a single product.  Scores of
+    about 35 in base-2 units, the terms all positive; the reference takes the query as the
+    kernel holds it (bf16 caches: a high and a low bf16 part)."""
     dev = torch.device("cuda")
-    gen = torch.Generator().manual_seed(64)
-    B, H, d = 128, 8, 64
+    gen = torch.Generator().manual_seed(d)
+    B, H = 128, 8
     q = 0.5 + torch.rand(B, H, d, generator=gen)
+    qs = q.double()
+    if kv_dtype == torch.bfloat16:
+        hi = q.to(torch.bfloat16)
+        qs = hi.double() + (q - hi.float()).to(torch.bfloat16).double()
     k = torch.zeros(B, H, 64, d)
-    k[:, :, 0] = (0.5 + torch.rand(B, H, d, generator=gen)) * 2.9
-    s0 = (q.double() * k[:, :, 0].double()).sum(-1)
-    k[:, :, 1, 0] = (s0 / q[..., 0].double()).float()
+    k[:, :, 0] = (0.5 + torch.rand(B, H, d, generator=gen)) * 2.9 * math.sqrt(64 / d)
+    k[:, :, 1, 0] = ((qs * k[:, :, 0].double()).sum(-1) / qs[..., 0]).float()
     v = torch.zeros(B, H, 64, d)
     v[:, :, 0] = 1.0
+    k, v = k.to(kv_dtype).to(dev), v.to(kv_dtype).to(dev)
     sl = torch.full((B,), 2, dtype=torch.int32, device=dev)
-    k, v = k.to(dev), v.to(dev)
     summ = eta.build_block_summaries(k, sl, 64, num_q_heads=H)
     tau = torch.full((B, H), float("-inf"), device=dev)
     out = eta.decode(q.to(dev), k, v, sl, summ, tau, block_size=64).out.cpu().double()[..., 0]
-    kc = k.cpu().double()
-    x = (q.double()[:, :, None] * kc[:, :, :2]).sum(-1) / math.sqrt(d) / math.log(2.0)
+    x = (qs[:, :, None] * k.cpu().double()[:, :, :2]).sum(-1) / math.sqrt(d) / math.log(2.0)
     assert 25 < x[..., 0].min() and x[..., 0].max() < 50
     w = torch.sigmoid((x[..., 0] - x[..., 1]) * math.log(2.0))
     err = (out - w) / (w * (1 - w) * math.log(2.0))
     rms = float(err.square().mean().sqrt())
-    say(f"[gpu] rms error of a base-2 score near 35: {rms:.2e}")
-    assert rms <= 3.2e-6
+    say(f"[gpu] d={d} {kv_dtype}: rms error of a base-2 score near 35: {rms:.2e}")
+    return rms
+
+
+def test_fp32_score_products_of_64_dims_are_summed_in_two_parts():
+    """A chain of n additions that rises evenly to s rounds by half an ulp of each partial sum,
+    rms 2^-24 s sqrt(n / 3) / sqrt(3) at most: 5.6e-6 for one chain of 64 (4.2e-6 with partial
+    sums spread over the ulp's binades), and two chains of 32 to s / 2 make half of it, 2.1e-6,
+    and the last addition 1.1e-6: 2.4e-6 together.  Bound: 3.2e-6."""
+    assert _score_error_rms(64, torch.float32) <= 3.2e-6
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_low_part_of_an_fp32_query_is_summed_first(d):
+    """bf16 caches: n = d / 8 matrix products of the query's high part and n of its low part.
+    The low part's sums are below 2^-8 s, so only the high part's n additions round: rms
+    2^-24 35 sqrt(n / 3) / sqrt(3), 2.0e-6 (d = 64) and 2.8e-6 (128), at most; after the high
+    part, each of the low part's would round at the score's size too, 1.1e-6 and 1.2e-6 a
+    time, sqrt(n) of them: 3.1e-6 and 4.7e-6 more.  The scaling to base-2 units adds 1.1e-6."""
+    n = d // 8
+    assert _score_error_rms(d, torch.bfloat16) <= math.hypot(2.0 ** -24 * 35 * math.sqrt(n) / 3, 1.2e-6)
 
 
 def test_decode_fp32_query_on_bf16_cache():
