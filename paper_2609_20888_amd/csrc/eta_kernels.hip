@@ -1384,14 +1384,13 @@ struct Bf16Tile {
     if (ntiles <= 0) return;
     // parts of V: a part of the next tile is requested when this tile's is consumed.  Two
     // where the gate leaves longer gaps (32 ragged sequences, 10%: 353.5 us with four,
-    // 350.4 with two; 512K equal) and for the dense baseline's uniform plan, one workgroup per
-    // compute unit (one 64K sequence, 16/4 heads, d = 128: 31.7 us with one, 29.5 with two,
-    // 29.2 with four; 512K: 174, 168, 176, 171 with sixteen; 4/4 heads, d = 64: 81 with two,
-    // 83 with sixteen); sixteen there for up to two heads of 128 (512K, 8/4: 163, 159) and for
-    // four of 64 (81, 82; with the heads' rows interleaved 97.6, 91); one for eight heads,
-    // whose p.V is longer (4 x 64K, 64/8: 187, two 192, four 195), and for the dense plan by
-    // length, two workgroups per unit (8 x 64K ragged, 32/8: 240, two 243).
-    constexpr int NCK = !DENSE ? 2 : PROP || G == 8 ? 1 : (D == 128 ? G <= 2 : G == 4) ? 16 : 2;
+    // 350.4 with two; 512K equal); sixteen for the dense baseline's uniform plan, one workgroup
+    // per compute unit, up to four heads (512K tokens, 16/4 heads, d = 128: 162.5 us with two
+    // and sixteen; 8/4: 162.0, 159.7; 16/4, d = 64: 81.4, 82.8, heads interleaved 96.5, 92.3;
+    // 4/4, d = 64: 80.5, 82.2, interleaved 95.5, 93.9); one for eight heads, whose p.V is longer
+    // (4 x 64K, 64/8: 187, two 192, four 195), and for the dense plan by length, two workgroups
+    // per unit (8 x 64K ragged, 32/8: 240, two 243).
+    constexpr int NCK = !DENSE ? 2 : PROP || G == 8 ? 1 : 16;
     constexpr int NR = NV / NCK;
     uint4 kr[DC];
     uint32_t vr[NV];
